@@ -20,7 +20,9 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssd.so")
-SOURCES = ["linear.hip", "attention.hip", "misc.hip", "sample.hip", "ssd_api.hip"]
+SOURCES = ["linear.hip", "gemv1.hip", "gemm.hip", "gemm_rows_store.hip", "gemm_rows_store_rms.hip",
+           "gemm_rows_resid.hip", "gemm_rows_qkv.hip", "gemm_rows_gated.hip",
+           "gemm_rows_argmax.hip", "attention.hip", "misc.hip", "sample.hip", "ssd_api.hip"]
 ARCH = "gfx950"
 
 

@@ -16,344 +16,394 @@
 #include "device.h"
 #include "kernels.h"
 
+#include <climits>
+
 namespace ssd {
 
 namespace {
 
-constexpr int QB = 8;
-
-template <typename KT, int DH>
-__device__ __forceinline__ const KT* key_row(const AttnArgs& a, const KT* base, int b, int h, int i,
-                                             bool& ok) {
-  if (a.cross) {
-    ok = true;
-    return base + ((size_t)(b * a.H + h) * a.n_keys + i) * DH;
-  }
-  const int pg_i = i / a.kv.page_size;
-  int page = -1;
-  if (pg_i < a.kv.max_pages) page = a.kv.page_table[(size_t)b * a.kv.max_pages + pg_i];
-  ok = page >= 0 && page < a.kv.n_pages;
-  if (!ok) page = 0;
-  const int slot = i - pg_i * a.kv.page_size;
-  return base + (((size_t)page * a.H + h) * a.kv.page_size + slot) * DH;
-}
-
-// Page-table entry of key i of sequence b (clamped to the table; validated where it is used).
-__device__ __forceinline__ int key_page(const AttnArgs& a, int b, int i) {
-  const int pg_i = min(i / a.kv.page_size, a.kv.max_pages - 1);
-  return a.kv.page_table[(size_t)b * a.kv.max_pages + pg_i];
-}
-
-// key_row for a page-table entry already loaded.
-template <typename KT, int DH>
-__device__ __forceinline__ const KT* key_row_at(const AttnArgs& a, const KT* base, int h, int i,
-                                                int page, bool& ok) {
-  ok = i / a.kv.page_size < a.kv.max_pages && page >= 0 && page < a.kv.n_pages;
-  if (!ok) page = 0;
-  const int slot = i - (i / a.kv.page_size) * a.kv.page_size;
-  return base + (((size_t)page * a.H + h) * a.kv.page_size + slot) * DH;
-}
-
-// Buffer-resource loads of key / value rows: 32-bit byte offsets from a pool base, and an offset
-// past the resource's range (ATTN_OOB) returns zeros without a memory access, so masked lanes
-// need no branch and cost no traffic.
-typedef uint32_t attn_u32x4 __attribute__((ext_vector_type(4)));
-constexpr uint32_t ATTN_OOB = 0x80000000u;
-constexpr size_t ATTN_RS_MAX = 0x7fff0000u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t attn_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-
-// Bytes of the key (or value) pool a launch may read from its base.
-template <typename KT, int DH>
-__host__ __device__ size_t attn_pool_bytes(const AttnArgs& a) {
-  const size_t row = (size_t)DH * sizeof(KT);
-  return a.cross ? (size_t)a.B * a.H * a.n_keys * row
-                 : (size_t)a.kv.n_pages * a.H * a.kv.page_size * row;
-}
-__device__ __forceinline__ void load_rs(Vec8<bf16_t>& v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  const attn_u32x4 t = __builtin_bit_cast(attn_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-  v.r = make_uint4(t.x, t.y, t.z, t.w);
-}
-__device__ __forceinline__ void load_rs(Vec8<float>& v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
-  const attn_u32x4 t0 = __builtin_bit_cast(attn_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-  const attn_u32x4 t1 =
-      __builtin_bit_cast(attn_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off + 16u, 0, 0));
-  v.a = make_float4(__uint_as_float(t0.x), __uint_as_float(t0.y), __uint_as_float(t0.z), __uint_as_float(t0.w));
-  v.b = make_float4(__uint_as_float(t1.x), __uint_as_float(t1.y), __uint_as_float(t1.z), __uint_as_float(t1.w));
-}
-
-// RS: the layer's key and value pools span less than 2 GiB and are read with buffer loads.
-template <typename KT, int DH, int QB, bool RS>
-__global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a, const int s_stride, const int ks) {
-  constexpr int CH = DH / 8;       // 16-byte chunks per key row (bf16) / 8-element groups
-  constexpr int KPI = 256 / CH;    // keys per block step in P.V
-  constexpr int KPW = 64 / CH;     // keys per wave step in P.V
-  constexpr int PF = 8;            // P.V loads in flight per thread
-  extern __shared__ float S[];     // [QB][s_stride] scores, then unnormalised probabilities
-  __shared__ float qs[QB][DH];
-  __shared__ float red[4][QB][DH];
-  __shared__ float inv_sum[QB];
-  __shared__ float row_max[QB], row_sum[QB];
-
-  // blockIdx.z = query group * ks + key split: this block's keys are [k0, k0 + nk) of the group's
-  // causal range (ks = 1: all of them)
-  const int h = blockIdx.x, b = blockIdx.y;
-  const int zq = blockIdx.z / ks, split = blockIdx.z - zq * ks, j0 = zq * QB;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nq = min(QB, a.C - j0);
-  const int HD = a.H * DH;
-  // Every load of the prologue is issued on every path (a masked lane reads zeros or a valid
-  // row, never skips the load): the wait counter retires loads in issue order, and a load skipped
-  // on one path makes the compiler wait for everything issued before the next one.
-  // The query rows first (they depend on nothing), then the page-table entries, the sequence
-  // length, the key row, the value chunks and the position bias.
-  constexpr int QPT = (QB * DH + 255) / 256;  // query elements per thread
-  float qv[QPT];
+// DT consecutive value elements as floats (8- or 16-byte loads).
+template <int DT>
+__device__ __forceinline__ void load_run(const float* p, float* f) {
 #pragma unroll
-  for (int t = 0; t < QPT; ++t) {
-    const int idx = min(tid + 256 * t, QB * DH - 1);
-    const int jq = min(idx / DH, nq - 1), d = idx - (idx / DH) * DH;
-    qv[t] = a.q[(size_t)(b * a.C + j0 + jq) * HD + h * DH + d];
+  for (int u = 0; u < DT / 4; ++u) {
+    const float4 v = reinterpret_cast<const float4*>(p)[u];
+    f[4 * u] = v.x; f[4 * u + 1] = v.y; f[4 * u + 2] = v.z; f[4 * u + 3] = v.w;
   }
-  // the sequence length as a vector load issued now (a scalar load would be issued where it is
-  // first used, after the key and value loads, and the bias would wait for it); cross-attention
-  // reads a placeholder
-  int vzero;
-  asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
-  const int* slp = a.cross ? reinterpret_cast<const int*>(a.q) : a.kv.seq_len + b;
-  const int seq_len_v = slp[vzero];
-  // self-attention key ranges do not depend on the sequence length (one split: from 0; several:
-  // fixed ranges of ceil(max_seq / ks) keys, the last ones empty while the context is short), so
-  // the page-table entries of this thread's first key row and value chunks are requested
-  // together with the sequence length, not after it
-  const bool pre = !a.cross;
-  const int kfix = ks == 1 ? 0 : (a.max_seq + ks - 1) / ks, kbase = split * kfix;
-  constexpr int PF0 = 8;  // value chunks prefetched per thread (PF below)
-  const int vk00 = tid / (DH / 8), kpi0 = 256 / (DH / 8);
-  int kpg = 0, vpg[PF0];
-  if (pre) {
-    kpg = key_page(a, b, kbase + tid);
+}
+template <int DT>
+__device__ __forceinline__ void load_run(const bf16_t* p, float* f) {
 #pragma unroll
-    for (int u = 0; u < PF0; ++u) vpg[u] = key_page(a, b, kbase + vk00 + kpi0 * u);
+  for (int u = 0; u < DT / 4; ++u) {
+    const uint2 v = reinterpret_cast<const uint2*>(p)[u];
+    f[4 * u] = __uint_as_float(v.x << 16); f[4 * u + 1] = __uint_as_float(v.x & 0xffff0000u);
+    f[4 * u + 2] = __uint_as_float(v.y << 16); f[4 * u + 3] = __uint_as_float(v.y & 0xffff0000u);
   }
-  const KT* Kb = reinterpret_cast<const KT*>(a.cross ? a.xk : a.kv.k);
-  const KT* Vb = reinterpret_cast<const KT*>(a.cross ? a.xv : a.kv.v);
+}
 
-  const int base = a.cross ? 0 : __builtin_amdgcn_readfirstlane(seq_len_v) + a.kv.pos_off;
-  const int nk_all = a.cross ? a.n_keys : base + j0 + nq;
-  const int per = ks == 1 ? nk_all : kfix;
-  const int k0 = min(nk_all, split * per);
-  int nk = min(nk_all, k0 + per) - k0;
-  if (nk > s_stride) {
+// One query row of one head: decode steps, and the rows of short chunks.  A block of NW waves per
+// (head, query row [, key split]); wave w takes the 16-key sub-tiles w, w + NW, ...: lane (c = l % 16,
+// g = l / 16) loads the same DT dims of the keys and of the values of keys 4 g + e (16 lanes cover a
+// row: whole cache lines a quarter-wave), so a score is DT products a lane and a sum over 16 lanes, and
+// the output is summed over g once at the end.  One barrier, where the waves' (max, sum, output) are
+// merged.  Bound: the chain sequence length / page entry -> key and value rows -> barrier.
+template <typename KT, int DH>
+struct RowDims {
+  static constexpr int DT = DH / 16;            // dims a lane holds, as 16- (or 8-) byte runs
+  static constexpr int RUN = sizeof(KT) == 4 ? 4 : (DT < 8 ? DT : 8);
+  static __device__ __forceinline__ int at(int c, int t) { return (t / RUN) * (16 * RUN) + c * RUN + t % RUN; }
+  static __device__ __forceinline__ void load(const KT* row, int c, float* f) {
+#pragma unroll
+    for (int u = 0; u < DT; u += RUN) load_run<RUN>(row + at(c, u), f + u);
+  }
+};
+
+// sum over the 16 lanes of a row of lanes (DPP rotations), in every lane
+__device__ __forceinline__ float row16_sum(float v) {
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x122, 0xf, 0xf, true));
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x121, 0xf, 0xf, true));
+  return v;
+}
+
+template <typename KT, int DH, int NW, bool CROSS, bool BIAS>
+__global__ __launch_bounds__(64 * NW) void attn_row_kernel(const AttnArgs a, const int per, const int ks,
+                                                           const uint32_t ps_inv, const uint32_t c_inv) {
+  constexpr int DT = DH / 16;
+  using D = RowDims<KT, DH>;
+  __shared__ float xo[NW][DH + 2];
+  // blockIdx.y: query row b C + j; blockIdx.z: the split of `per` keys (per 0: all of them)
+  const int h = blockIdx.x, r = blockIdx.y, split = blockIdx.z;
+  const int b = (int)__umulhi((uint32_t)(2 * r + 1), c_inv), j = r - b * a.C;  // as page_index below
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15, HD = a.H * DH;
+
+  // the sequence length as a vector load issued with the first page-table entries (neither depends
+  // on the other: splits are fixed ranges of the capacity, and lanes past the context are masked)
+  int seq_len_v = 0;
+  if (!CROSS) {
+    int vzero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
+    seq_len_v = a.kv.seq_len[b + vzero];
+  }
+  const int ps = a.kv.page_size;
+  // i / ps as floor((2 i + 1) ps_inv / 2^32), ps_inv = floor(2^31 / ps) + 1: exact for i, ps < 2^15
+  auto page_index = [&](int i) { return (int)__umulhi((uint32_t)(2 * i + 1), ps_inv); };
+  const int k0 = split * per;
+  int t0 = k0 + 16 * wave;  // first key of the wave's current sub-tile
+  int pg[4];
+  auto entries = [&](int t) {  // page-table entries of this lane's keys (clamped to the table)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      pg[e] = CROSS ? 0 : a.kv.page_table[(size_t)b * a.kv.max_pages + min(page_index(t + 4 * g + e), a.kv.max_pages - 1)];
+  };
+  entries(t0);
+  float q[DT];
+#pragma unroll
+  for (int u = 0; u < DT; u += D::RUN) load_run<D::RUN>(a.q + (size_t)r * HD + h * DH + D::at(c, u), q + u);
+  const KT* Kb = reinterpret_cast<const KT*>(CROSS ? a.xk : a.kv.k);
+  const KT* Vb = reinterpret_cast<const KT*>(CROSS ? a.xv : a.kv.v);
+#pragma unroll
+  for (int t = 0; t < DT; ++t) q[t] *= a.scale;
+
+  const int pq = CROSS ? 0 : __builtin_amdgcn_readfirstlane(seq_len_v) + a.kv.pos_off + j;
+  int nk = CROSS ? a.n_keys : pq + 1;
+  if (!CROSS && nk > a.max_seq) {
     if (tid == 0) atomicOr(a.status, SSD_DEV_CAPACITY);
-    nk = s_stride;
+    nk = a.max_seq;
   }
+  const int k_end = per ? min(nk, k0 + per) : nk;
+  const float* bias = BIAS ? a.bias + (size_t)h * a.max_seq : nullptr;
 
-  // the first key row and the first value chunks, before any barrier.  Self-attention addresses
-  // them from the split's fixed start (a non-empty split starts there) and the page-table
-  // entries.  Lanes past nk (and rows of a missing page) are masked: buffer loads with an
-  // out-of-range offset (RS), else a clamped valid row.
-  const int clast = a.n_keys - 1;
-  const uint32_t pool_rs = RS ? (uint32_t)attn_pool_bytes<KT, DH>(a) : 0u;
-  const __amdgpu_buffer_rsrc_t krs = attn_rsrc(Kb, pool_rs), vrs = attn_rsrc(Vb, pool_rs);
-  bool kok = false;
-  Vec8<KT> krow[CH];
+  float m_run = -INFINITY, l_run = 0.f, o[DT];  // l_run, o: this lane's keys only, summed at the end
+#pragma unroll
+  for (int t = 0; t < DT; ++t) o[t] = 0.f;
+  for (; t0 < k_end; t0 += 16 * NW) {
+    float kf[4][DT], vf[4][DT], bv[4];
+    bool ok[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int ki = t0 + 4 * g + e;
+      size_t off;
+      if (CROSS) {
+        ok[e] = ki < k_end;
+        off = ((size_t)(b * a.H + h) * a.n_keys + min(ki, a.n_keys - 1)) * DH;
+      } else {
+        const int pi = page_index(ki);
+        ok[e] = ki < k_end && pi < a.kv.max_pages && pg[e] >= 0 && pg[e] < a.kv.n_pages;
+        off = (((size_t)(ok[e] ? pg[e] : 0) * a.H + h) * ps + (ki - pi * ps)) * DH;
+      }
+      D::load(Kb + off, c, kf[e]);
+      D::load(Vb + off, c, vf[e]);
+      bv[e] = BIAS ? bias[min(max(pq - ki, 0), a.max_seq - 1)] : 0.f;
+    }
+    float sc[4], mt = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float s = 0.f;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) s = fmaf(kf[e][t], q[t], s);
+      s = row16_sum(s);
+      sc[e] = ok[e] ? s + bv[e] : -INFINITY;
+      mt = fmaxf(mt, sc[e]);
+    }
+    mt = fmaxf(mt, __shfl_xor(mt, 16, SSD_WAVE));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, SSD_WAVE));
+    const float m_new = fmaxf(m_run, mt);
+    const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - m_new);
+    l_run *= alpha;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) o[t] *= alpha;
+    m_run = m_new;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float p = sc[e] == -INFINITY ? 0.f : expf(sc[e] - m_new);
+      l_run += p;
+      // a value row past the context may hold anything: it enters as zeros
+#pragma unroll
+      for (int t = 0; t < DT; ++t) o[t] = fmaf(p, ok[e] ? vf[e][t] : 0.f, o[t]);
+    }
+    if (t0 + 16 * NW < k_end) entries(t0 + 16 * NW);
+  }
+  l_run += __shfl_xor(l_run, 16, SSD_WAVE);
+  l_run += __shfl_xor(l_run, 32, SSD_WAVE);
+#pragma unroll
+  for (int t = 0; t < DT; ++t) {
+    o[t] += __shfl_xor(o[t], 16, SSD_WAVE);
+    o[t] += __shfl_xor(o[t], 32, SSD_WAVE);
+  }
+  if (g == 0) {
+#pragma unroll
+    for (int t = 0; t < DT; ++t) xo[wave][D::at(c, t)] = o[t];
+    if (c == 0) {
+      xo[wave][DH] = m_run;
+      xo[wave][DH + 1] = l_run;
+    }
+  }
+  __syncthreads();
+  if (tid >= DH) return;
+  float m = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) m = fmaxf(m, xo[w][DH]);
+  float l = 0.f, y = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float mw = xo[w][DH], f = mw == -INFINITY ? 0.f : expf(mw - m);
+    l = fmaf(f, xo[w][DH + 1], l);
+    y = fmaf(f, xo[w][tid], y);
+  }
+  if (per) {
+    // partial of this key split: unnormalised output, row max and sum (attn_combine_kernel)
+    float* pp = a.part + (((size_t)r * a.H + h) * ks + split) * (DH + 2);
+    pp[tid] = y;
+    if (tid == 0) {
+      pp[DH] = m;
+      pp[DH + 1] = l;
+    }
+    return;
+  }
+  y = l > 0.f ? y / l : 0.f;
+  if (a.out) a.out[(size_t)r * HD + h * DH + tid] = y;
+  if (a.out_planes) store_planes1(a.out_planes + plane_at(r, h * DH + tid, (a.B * a.C + 15) >> 4), y);
+}
+
+// Attention of 16 query rows of one head on float32 matrix products (v_mfma_f32_16x16x4_f32), for
+// single rows, verify chunks and prefill blocks, paged or cross, float32 or bf16 keys.  One block
+// of NW waves per (head, sequence, 16 rows [, key split]); wave w takes the 16-key sub-tiles
+// w, w + NW, ... of the block's keys, straight from memory into registers: lane (c = l % 16,
+// g = l / 16) loads a quarter (dims DQ g ..) of key c and of query c, so that S^T = K . Q^T runs
+// over the lanes' elements in order, and the dims DT c .. of the values of keys 4 g + e, so that
+// O^T += V^T . P^T takes the lane's own probabilities as its B operand.  Nothing is staged in LDS
+// and there is one barrier, where the waves' (max, sum, output) are merged.  The sums are float32
+// products and sums throughout, as in a vector kernel.
+// CROSS and BIAS are template parameters so that no branch stands between the first loads.
+template <typename KT, int DH, int NW, bool CROSS, bool BIAS>
+__global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, const int per, const int ks, const uint32_t ps_inv) {
+  constexpr int DQ = DH / 4;   // elements of a key (and query) row per lane
+  constexpr int DT = DH / 16;  // output tiles; consecutive value elements per lane
+  extern __shared__ __attribute__((aligned(16))) float xo[];  // [NW][DQ + 2][64]
+  // blockIdx.z: the 16-row group, or (per > 0, at most 16 rows) the split of `per` keys
+  const int h = blockIdx.x, b = blockIdx.y;
+  const int split = per ? blockIdx.z : 0, j0 = per ? 0 : blockIdx.z * 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int nq = min(16, a.C - j0), HD = a.H * DH;
+
+  // the sequence length as a vector load issued with the first page-table entries (neither depends
+  // on the other: splits are fixed ranges of the capacity, and lanes past the context are masked)
+  int seq_len_v = 0;
+  if (!CROSS) {
+    int vzero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
+    seq_len_v = a.kv.seq_len[b + vzero];
+  }
+  const int ps = a.kv.page_size;
+  // i / ps as floor((2 i + 1) ps_inv / 2^32), ps_inv = floor(2^31 / ps) + 1: exact for i, ps < 2^15
+  auto page_index = [&](int i) { return (int)__umulhi((uint32_t)(2 * i + 1), ps_inv); };
+  auto entry = [&](int i) {  // page-table entry of key i (clamped to the table)
+    return CROSS ? 0 : a.kv.page_table[(size_t)b * a.kv.max_pages + min(page_index(i), a.kv.max_pages - 1)];
+  };
+  // row of key i, given its page-table entry; ok: the key exists (its page is mapped)
+  auto row = [&](const KT* base, int i, int page, bool& ok) {
+    if (CROSS) {
+      ok = i < a.n_keys;
+      return base + ((size_t)(b * a.H + h) * a.n_keys + min(i, a.n_keys - 1)) * DH;
+    }
+    const int pi = page_index(i);
+    ok = pi < a.kv.max_pages && page >= 0 && page < a.kv.n_pages;
+    return base + (((size_t)(ok ? page : 0) * a.H + h) * ps + (i - pi * ps)) * DH;
+  };
+  const KT* Kb = reinterpret_cast<const KT*>(CROSS ? a.xk : a.kv.k);
+  const KT* Vb = reinterpret_cast<const KT*>(CROSS ? a.xv : a.kv.v);
+
+  const int k0 = split * per;
+  int t0 = k0 + 16 * wave;  // first key of the wave's current sub-tile
+  int kpg = entry(t0 + c), vpg[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) vpg[e] = entry(t0 + 4 * g + e);
+
+  float q[DQ];
   {
-    const KT* kp = pre ? key_row_at<KT, DH>(a, Kb, h, kbase + tid, kpg, kok)
-                       : key_row<KT, DH>(a, Kb, b, h, min(tid, clast), kok);
-    kok = kok && tid < nk;
-    if constexpr (RS) {
-      const uint32_t off = kok ? (uint32_t)((size_t)(kp - Kb) * sizeof(KT)) : ATTN_OOB;
+    const float* qrow = a.q + (size_t)(b * a.C + j0 + min(c, nq - 1)) * HD + h * DH + DQ * g;
 #pragma unroll
-      for (int c = 0; c < CH; ++c) load_rs(krow[c], krs, off + 8u * c * sizeof(KT));
-    } else {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) krow[c].load(kp + 8 * c);
+    for (int u = 0; u < DQ / 4; ++u) {
+      const float4 v = reinterpret_cast<const float4*>(qrow)[u];
+      q[4 * u] = v.x * a.scale; q[4 * u + 1] = v.y * a.scale;
+      q[4 * u + 2] = v.z * a.scale; q[4 * u + 3] = v.w * a.scale;
     }
   }
-  const int vc = tid % CH, vk0 = tid / CH;
-  static_assert(PF == PF0, "value prefetch depth");
-  Vec8<KT> vpre[PF];
-  bool vok[PF];
-#pragma unroll
-  for (int u = 0; u < PF; ++u) {
-    const int i = vk0 + KPI * u;
-    const KT* vp = pre ? key_row_at<KT, DH>(a, Vb, h, kbase + i, vpg[u], vok[u])
-                       : key_row<KT, DH>(a, Vb, b, h, min(i, clast), vok[u]);
-    vok[u] = vok[u] && i < nk;
-    if constexpr (RS) {
-      const uint32_t off = vok[u] ? (uint32_t)((size_t)(vp - Vb + 8 * vc) * sizeof(KT)) : ATTN_OOB;
-      load_rs(vpre[u], vrs, off);
-    } else {
-      vpre[u].load(vp + 8 * vc);
-    }
+  const int base = CROSS ? 0 : __builtin_amdgcn_readfirstlane(seq_len_v) + a.kv.pos_off;
+  int nk = CROSS ? a.n_keys : base + j0 + nq;
+  if (!CROSS && nk > a.max_seq) {
+    if (tid == 0) atomicOr(a.status, SSD_DEV_CAPACITY);
+    nk = a.max_seq;
   }
-  // T5 position bias of this thread's first key for each query row (LLaMA and cross-attention:
-  // a placeholder read of the query)
-  float bpre[QB];
-  {
-    const float* bsrc = (a.bias && !a.cross) ? a.bias + (size_t)h * a.max_seq : a.q;
-#pragma unroll
-    for (int jq = 0; jq < QB; ++jq) {
-      const int dist = base + j0 + jq - (k0 + tid);
-      bpre[jq] = bsrc[(a.bias && !a.cross) ? min(max(dist, 0), a.max_seq - 1) : 0];
-    }
-  }
+  const int k_end = per ? min(nk, k0 + per) : nk;
+  const int pq = CROSS ? INT_MAX : base + j0 + min(c, nq - 1);  // this lane's query position
+  const float* bias = BIAS ? a.bias + (size_t)h * a.max_seq : nullptr;
 
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's keys only, summed at the end
+  f32x4_t acc[DT];
 #pragma unroll
-  for (int t = 0; t < QPT; ++t) {
-    const int idx = tid + 256 * t;
-    if (idx < QB * DH) {
-      const int jq = idx / DH, d = idx - jq * DH;
-      qs[jq][d] = jq < nq ? qv[t] * a.scale : 0.f;
-    }
-  }
-  __syncthreads();
+  for (int t = 0; t < DT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // scores: one key per thread per step (i relative to k0)
-  for (int i = tid; i < nk; i += 256) {
-    // query blocks and 512-byte key rows: the query reads stay inside the loop (hoisted out of
-    // it they pin up to 8 rows of registers, and spill with float keys at dh 128); a one-row
-    // block with a short key row keeps them hoisted
-    if constexpr (QB > 1 || DH * sizeof(KT) > 256) asm volatile("" ::: "memory");
-    bool ok = kok;
-    if (i != tid) {
-      const KT* kp = key_row<KT, DH>(a, Kb, b, h, k0 + i, ok);
-      if (ok) {
+  for (; t0 < k_end; t0 += 16 * NW) {
+    bool kok, vok[4];
+    float kf[DQ], vf[4][DT], bv[4];
+    {
+      const KT* kp = row(Kb, t0 + c, kpg, kok) + DQ * g;
+      Vec8<KT> r[DQ / 8];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) krow[c].load(kp + 8 * c);
-      }
-    }
-    float dots[QB];
+      for (int u = 0; u < DQ / 8; ++u) r[u].load(kp + 8 * u);
 #pragma unroll
-    for (int jq = 0; jq < QB; ++jq) dots[jq] = 0.f;
-    if (ok) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        float kf[8];
-        krow[c].to_f32(kf);
-        // every row of the block (rows past nq hold zeros and are masked below): no branch
-        // between the LDS reads of the rows, so they are issued together
-#pragma unroll
-        for (int jq = 0; jq < QB; ++jq) {
-          float t = dots[jq];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) t = fmaf(qs[jq][8 * c + e], kf[e], t);
-          dots[jq] = t;
-        }
-      }
+      for (int u = 0; u < DQ / 8; ++u) r[u].to_f32(kf + 8 * u);
     }
 #pragma unroll
-    for (int jq = 0; jq < QB; ++jq) {
-      float sc = dots[jq];
-      if (!ok || jq >= nq) {
-        sc = -INFINITY;
-      } else if (!a.cross) {
-        const int p = base + j0 + jq, ki = k0 + i;
-        if (ki > p) sc = -INFINITY;
-        else if (a.bias && p - ki < a.max_seq)
-          sc += i == tid ? bpre[jq] : a.bias[(size_t)h * a.max_seq + (p - ki)];
-      }
-      S[jq * s_stride + i] = sc;
+    for (int e = 0; e < 4; ++e) {
+      const int ki = t0 + 4 * g + e;
+      const KT* vp = row(Vb, ki, vpg[e], vok[e]) + DT * c;
+      load_run<DT>(vp, vf[e]);
+      vok[e] = vok[e] && ki < k_end;
+      bv[e] = BIAS ? bias[min(max(pq - ki, 0), a.max_seq - 1)] : 0.f;
+    }
+    // scores, two chains: D[key 4 g + e][query c]
+    f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+    for (int u = 0; u < DQ; u += 2) {
+      s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u], q[u], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u + 1], q[u + 1], s1, 0, 0, 0);
+    }
+    float sc[4], mt = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // vok: the key is in the context and on a mapped page (a value row and its key row share it)
+      sc[e] = (vok[e] && t0 + 4 * g + e <= pq) ? s0[e] + s1[e] + bv[e] : -INFINITY;
+      mt = fmaxf(mt, sc[e]);
+    }
+    mt = fmaxf(mt, __shfl_xor(mt, 16, SSD_WAVE));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, SSD_WAVE));
+    const float m_new = fmaxf(m_run, mt);
+    const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - m_new);
+    float ls = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[e] = sc[e] == -INFINITY ? 0.f : expf(sc[e] - m_new);
+      ls += sc[e];
+    }
+    l_run = l_run * alpha + ls;
+    m_run = m_new;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[t] *= alpha;
+    // a value row past the context may hold anything: it enters the products as zeros
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vok[e] ? vf[e][t] : 0.f, sc[e], acc[t], 0, 0, 0);
+    const int tn = t0 + 16 * NW;
+    if (tn < k_end) {
+      kpg = entry(tn + c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) vpg[e] = entry(tn + 4 * g + e);
     }
   }
-  __syncthreads();
+  l_run += __shfl_xor(l_run, 16, SSD_WAVE);
+  l_run += __shfl_xor(l_run, 32, SSD_WAVE);
 
-  // softmax numerators, one wave per row
-  for (int jq = wave; jq < nq; jq += 4) {
-    float* row = S + jq * s_stride;
-    float m = -INFINITY;
-    for (int i = lane; i < nk; i += 64) m = fmaxf(m, row[i]);
-    m = wave_max(m);
-    float sum = 0.f;
-    for (int i = lane; i < nk; i += 64) {
-      const float e = (m == -INFINITY || row[i] == -INFINITY) ? 0.f : expf(row[i] - m);
-      row[i] = e;
-      sum += e;
-    }
-    sum = wave_sum(sum);
-    if (lane == 0) {
-      inv_sum[jq] = sum > 0.f ? 1.0f / sum : 0.f;
-      row_max[jq] = m;
-      row_sum[jq] = sum;
-    }
-  }
+  // acc[t][e] is output dim DQ g + DT e + t of query c: the wave's triple goes to LDS lane-major;
+  // then wave w < 4 merges the waves' dims DT w .. of every lane's quarter
+  float* mine = xo + (size_t)wave * (DQ + 2) * 64 + lane;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int t = 0; t < DT; ++t) mine[(DT * e + t) * 64] = acc[t][e];
+  mine[DQ * 64] = m_run;
+  mine[(DQ + 1) * 64] = l_run;
   __syncthreads();
-
-  // P . V: thread (key group vk0, chunk vc) accumulates 8 dims of every query row
-  float acc[QB][8];
+  if (wave >= 4 || c >= nq) return;
+  const float* all = xo + lane;
+  float m = -INFINITY;
 #pragma unroll
-  for (int jq = 0; jq < QB; ++jq)
+  for (int w = 0; w < NW; ++w) m = fmaxf(m, all[((size_t)w * (DQ + 2) + DQ) * 64]);
+  float l = 0.f, o[DT];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[jq][e] = 0.f;
-  for (int u0 = 0; vk0 + KPI * u0 < nk; u0 += PF) {
-    if (u0 > 0) {
+  for (int t = 0; t < DT; ++t) o[t] = 0.f;
 #pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        const int i = vk0 + KPI * (u0 + u);
-        vok[u] = false;
-        if (i < nk) {
-          const KT* vp = key_row<KT, DH>(a, Vb, b, h, k0 + i, vok[u]);
-          if (vok[u]) vpre[u].load(vp + 8 * vc);
-        }
-      }
-    }
+  for (int w = 0; w < NW; ++w) {
+    const float* tw = all + (size_t)w * (DQ + 2) * 64;
+    const float mw = tw[DQ * 64], f = mw == -INFINITY ? 0.f : expf(mw - m);
+    l = fmaf(f, tw[(DQ + 1) * 64], l);
 #pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const int i = vk0 + KPI * (u0 + u);
-      if (i < nk && vok[u]) {
-        float vf[8];
-        vpre[u].to_f32(vf);
-#pragma unroll
-        for (int jq = 0; jq < QB; ++jq) {
-          // rows past nq (scores never turned into probabilities) contribute nothing
-          const float sp = S[jq * s_stride + i];
-          const float p = jq < nq ? sp : 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[jq][e] = fmaf(p, vf[e], acc[jq][e]);
-        }
-      }
-    }
+    for (int t = 0; t < DT; ++t) o[t] = fmaf(f, tw[(DT * wave + t) * 64], o[t]);
   }
-  // reduce over the key groups of the wave (lanes that share vc), then over waves
+  const int d0 = DQ * g + DT * wave;
+  const size_t r = (size_t)b * a.C + j0 + c;
+  if (per) {
+    // partial of this key split: unnormalised output, row max and sum (attn_combine_kernel)
+    float* pp = a.part + ((r * a.H + h) * ks + split) * (DH + 2);
 #pragma unroll
-  for (int jq = 0; jq < QB; ++jq)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float v = acc[jq][e];
-#pragma unroll
-      for (int o = CH; o < 64; o <<= 1) v += __shfl_xor(v, o, SSD_WAVE);
-      acc[jq][e] = v;
+    for (int t = 0; t < DT; ++t) pp[d0 + t] = o[t];
+    if (wave == 0 && g == 0) {
+      pp[DH] = m;
+      pp[DH + 1] = l;
     }
-  if (lane < CH) {
-#pragma unroll
-    for (int jq = 0; jq < QB; ++jq)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) red[wave][jq][8 * lane + e] = acc[jq][e];
+    return;
   }
-  __syncthreads();
-  for (int idx = tid; idx < nq * DH; idx += 256) {
-    const int jq = idx / DH, d = idx - jq * DH;
-    const float v = (red[0][jq][d] + red[1][jq][d]) + (red[2][jq][d] + red[3][jq][d]);
-    if (ks > 1) {
-      // partial of this key split: unnormalised output, row max and sum (attn_combine_kernel)
-      float* pp = a.part + (((size_t)(b * a.C + j0 + jq) * a.H + h) * ks + split) * (DH + 2);
-      pp[d] = v;
-      if (d == 0) {
-        pp[DH] = row_max[jq];
-        pp[DH + 1] = row_sum[jq];
-      }
-      continue;
-    }
-    const size_t o = (size_t)(b * a.C + j0 + jq) * HD + h * DH + d;
-    a.out[o] = v * inv_sum[jq];
-    if (a.out_planes) {  // hi / lo bf16 planes for the skinny MFMA consumer (rows < plane_rows)
-      const float y = v * inv_sum[jq];
-      const uint32_t hi = f32_to_bf16(y);
-      a.out_planes[o] = (bf16_t)hi;
-      a.out_planes[o + (size_t)a.plane_rows * HD] = (bf16_t)f32_to_bf16(y - bf16_to_f32(hi));
-    }
+  const float inv = l > 0.f ? 1.0f / l : 0.f;
+  const size_t oi = r * HD + h * DH + d0;
+#pragma unroll
+  for (int t = 0; t < DT; ++t) o[t] *= inv;
+  if (a.out) {
+#pragma unroll
+    for (int t = 0; t < DT; t += 4)
+      *reinterpret_cast<float4*>(a.out + oi + t) = make_float4(o[t], o[t + 1], o[t + 2], o[t + 3]);
+  }
+  if (a.out_planes) {  // operand planes for the next projection
+#pragma unroll
+    for (int t = 0; t < DT; t += 4)
+      store_planes4(a.out_planes + plane_at((int)r, h * DH + d0 + t, (a.B * a.C + 15) >> 4), o[t], o[t + 1],
+                    o[t + 2], o[t + 3]);
   }
 }
 
@@ -387,12 +437,8 @@ __global__ __launch_bounds__(DH) void attn_combine_kernel(const AttnArgs a, cons
     }
   const float y = l > 0.f ? o / l : 0.f;
   const size_t oi = (size_t)r * HD + h * DH + d;
-  a.out[oi] = y;
-  if (a.out_planes) {
-    const uint32_t hi = f32_to_bf16(y);
-    a.out_planes[oi] = (bf16_t)hi;
-    a.out_planes[oi + (size_t)a.plane_rows * HD] = (bf16_t)f32_to_bf16(y - bf16_to_f32(hi));
-  }
+  if (a.out) a.out[oi] = y;
+  if (a.out_planes) store_planes1(a.out_planes + plane_at(r, h * DH + d, (a.B * a.C + 15) >> 4), y);
 }
 
 // Causal self-attention of a prefill block on MFMA (float32 cache, no position bias): one block of
@@ -677,11 +723,16 @@ __global__ __launch_bounds__(512) void attn_mfma_kernel(const AttnArgs a, const 
   // lane: O^T[16 t + 4 g + e][query c16]
   if (16 * wave + c16 < nq) {
     const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
-    float* orow = a.out + (size_t)(b * a.C + j0 + 16 * wave + c16) * HD + h * DH;
+    const size_t oi = (size_t)(b * a.C + j0 + 16 * wave + c16) * HD + h * DH;
 #pragma unroll
-    for (int t = 0; t < ND; ++t)
-      *reinterpret_cast<float4*>(orow + 16 * t + 4 * g) =
-          make_float4(acc_o[t][0] * inv, acc_o[t][1] * inv, acc_o[t][2] * inv, acc_o[t][3] * inv);
+    for (int t = 0; t < ND; ++t) {
+      const size_t o = oi + 16 * t + 4 * g;
+      const f32x4_t v = acc_o[t] * inv;
+      if (a.out) *reinterpret_cast<float4*>(a.out + o) = make_float4(v[0], v[1], v[2], v[3]);
+      if (a.out_planes)
+        store_planes4(a.out_planes + plane_at(b * a.C + j0 + 16 * wave + c16, h * DH + 16 * t + 4 * g, (a.B * a.C + 15) >> 4),
+                      v[0], v[1], v[2], v[3]);
+    }
   }
 }
 
@@ -699,7 +750,7 @@ size_t attn_mfma_shm(const AttnArgs& a) {
 // The MFMA prefill attention applies: self-attention of more than 16 rows a sequence over a
 // float32 cache whose pages hold 2..64 keys dividing 64, no position bias, no output planes.
 bool attn_mfma_ok(const AttnArgs& a) {
-  if (a.cross || a.C <= 16 || a.kvdtype != 0 || a.bias || a.out_planes || a.kv.page_size < 2 ||
+  if (a.cross || a.C <= 16 || a.kvdtype != 0 || a.bias || a.kv.page_size < 2 ||
       64 % a.kv.page_size || (a.dh != 64 && a.dh != 128))
     return false;
   const size_t shm = a.dh == 64 ? attn_mfma_shm<64>(a) : attn_mfma_shm<128>(a);
@@ -991,39 +1042,58 @@ int attn_splits(const AttnArgs& a, int groups) {
   return ks < 1 ? 1 : ks;
 }
 
+template <typename KT, int DH, int NW, bool CROSS, bool BIAS>
+void launch_attn_rows_t(const AttnArgs& a, int groups, int ks, hipStream_t s) {
+  constexpr size_t shm = (size_t)NW * (DH / 4 + 2) * 64 * sizeof(float);
+  if constexpr (shm > 64 * 1024) {
+    static bool attr = false;
+    if (!attr) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_rows_kernel<KT, DH, NW, CROSS, BIAS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+      attr = true;
+    }
+  }
+  const uint32_t ps_inv = CROSS ? 0u : (1u << 31) / (uint32_t)a.kv.page_size + 1u;
+  const int per = ks > 1 ? ((a.max_seq + ks - 1) / ks + 15) / 16 * 16 : 0;
+  hipLaunchKernelGGL((attn_rows_kernel<KT, DH, NW, CROSS, BIAS>), dim3(a.H, a.B, groups * ks), dim3(64 * NW),
+                     shm, s, a, per, ks, ps_inv);
+}
+
+template <typename KT, int DH, int NW>
+void launch_attn_rows(const AttnArgs& a, int groups, int ks, hipStream_t s) {
+  if (a.cross) launch_attn_rows_t<KT, DH, NW, true, false>(a, groups, ks, s);
+  else if (a.bias) launch_attn_rows_t<KT, DH, NW, false, true>(a, groups, ks, s);
+  else launch_attn_rows_t<KT, DH, NW, false, false>(a, groups, ks, s);
+}
+
+template <typename KT, int DH, int NW, bool CROSS, bool BIAS>
+void launch_attn_row_t(const AttnArgs& a, int ks, hipStream_t s) {
+  const uint32_t ps_inv = CROSS ? 0u : (1u << 31) / (uint32_t)a.kv.page_size + 1u;
+  const int per = ks > 1 ? ((a.max_seq + ks - 1) / ks + 15) / 16 * 16 : 0;
+  hipLaunchKernelGGL((attn_row_kernel<KT, DH, NW, CROSS, BIAS>), dim3(a.H, a.B * a.C, ks), dim3(64 * NW), 0, s,
+                     a, per, ks, ps_inv, (1u << 31) / (uint32_t)a.C + 1u);
+}
+
+template <typename KT, int DH>
+void launch_attn_row(const AttnArgs& a, int ks, hipStream_t s) {
+  if (a.cross && a.n_keys <= 64) launch_attn_row_t<KT, DH, 4, true, false>(a, ks, s);
+  else if (a.cross) launch_attn_row_t<KT, DH, 8, true, false>(a, ks, s);
+  else if (a.bias) launch_attn_row_t<KT, DH, 8, false, true>(a, ks, s);
+  else launch_attn_row_t<KT, DH, 8, false, false>(a, ks, s);
+}
+
 template <typename KT, int DH>
 hipError_t launch_attn_dh(const AttnArgs& a, hipStream_t s) {
-  const int nk_max = a.cross ? a.n_keys : a.max_seq;
-  const bool long_ctx = !a.cross && a.max_seq >= 256;
-  const bool rs = attn_pool_bytes<KT, DH>(a) <= ATTN_RS_MAX;
-  int ks = 1;
-  if (a.C == 1 || (a.C <= 16 && !long_ctx)) {
-    // decode steps and short-context verify chunks: one block per (head, sequence, query row
-    // [, key split]); the rows of a chunk re-read the same few keys from L2, and more blocks keep
-    // the chip busy
-    ks = attn_splits(a, a.C);
-    const int s_stride = (((nk_max + ks - 1) / ks) + 63) & ~63;
-    dim3 grid(a.H, a.B, a.C * ks);
-    const size_t shm = (size_t)s_stride * sizeof(float);
-    if (rs)
-      hipLaunchKernelGGL((attn_kernel<KT, DH, 1, true>), grid, dim3(256), shm, s, a, s_stride, ks);
-    else
-      hipLaunchKernelGGL((attn_kernel<KT, DH, 1, false>), grid, dim3(256), shm, s, a, s_stride, ks);
-  } else {
-    // prefill blocks and long-context verify chunks: up to QB rows of a sequence share each key
-    // load (and long contexts split their keys)
-    const int groups = (a.C + QB - 1) / QB;
-    ks = attn_splits(a, groups);
-    const int s_stride = (((nk_max + ks - 1) / ks) + 63) & ~63;
-    dim3 grid(a.H, a.B, groups * ks);
-    const size_t shm = (size_t)QB * s_stride * sizeof(float);
-    if (sizeof(KT) == 4 && attn_chunk_ok(a, ks))
-      launch_attn_chunk<DH>(a, ks, s);
-    else if (rs)
-      hipLaunchKernelGGL((attn_kernel<KT, DH, QB, true>), grid, dim3(256), shm, s, a, s_stride, ks);
-    else
-      hipLaunchKernelGGL((attn_kernel<KT, DH, QB, false>), grid, dim3(256), shm, s, a, s_stride, ks);
-  }
+  const int groups = (a.C + 15) / 16, ks = attn_splits(a, groups);
+  // Single rows, and the rows of chunks short in rows and context while their blocks are about two
+  // rounds of the chip (6 rows x 32 heads at a capacity of 204 keys: 4.9 us against 6.2 for the
+  // 16-row kernel; 4 rows x 96 heads over 1000 keys: 20.4 against 17.7)
+  const bool by_row = a.C == 1 || (a.C <= 8 && (a.cross ? a.n_keys <= 64 : a.max_seq < 256) &&
+                                   (long long)a.H * a.B * a.C <= 2LL * cu_count());
+  if (by_row) launch_attn_row<KT, DH>(a, ks, s);
+  else if (sizeof(KT) == 4 && attn_chunk_ok(a, ks)) launch_attn_chunk<DH>(a, ks, s);
+  else if ((a.cross ? a.n_keys : a.max_seq) <= 64) launch_attn_rows<KT, DH, 4>(a, groups, ks, s);
+  else launch_attn_rows<KT, DH, 8>(a, groups, ks, s);
   if (ks > 1) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

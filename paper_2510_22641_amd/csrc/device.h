@@ -58,6 +58,32 @@ __device__ __forceinline__ void split_bf16x8_v(const float4& a0, const float4& a
                   pack_bf16x2(a1.z - __uint_as_float(h3 << 16), a1.w - __uint_as_float(h3 & 0xffff0000u)));
 }
 
+// Operand planes of activations: the hi and lo bf16 planes of a matrix of rows in the order the
+// matrix instructions take them, a fragment of 16 rows x 32 elements as 64 lanes x 16 bytes (lane
+// 16 ((k / 8) % 4) + m % 16), hi and lo fragments side by side, row groups within K blocks.  A
+// wave's operand load is then one contiguous kilobyte, where rows a power of two apart would send
+// its 16 rows to the same few cache channels.  Element (m, k) of `ng` row groups; lo at
+// + PLANE_LO.
+constexpr int PLANE_FRAG = 1024;  // bf16 of a hi + lo fragment pair
+constexpr int PLANE_LO = 512;
+__device__ __forceinline__ size_t plane_at(int m, int k, int ng) {
+  return ((size_t)(k >> 5) * ng + (m >> 4)) * PLANE_FRAG + ((((k >> 3) & 3) << 4) + (m & 15)) * 8 + (k & 7);
+}
+
+// hi / lo of one value, or of four consecutive elements (k a multiple of 4) of a row.
+__device__ __forceinline__ void store_planes1(bf16_t* hi, float v) {
+  const uint32_t h = f32_to_bf16(v);
+  hi[0] = (bf16_t)h;
+  hi[PLANE_LO] = (bf16_t)f32_to_bf16(v - bf16_to_f32(h));
+}
+__device__ __forceinline__ void store_planes4(bf16_t* hi, float a, float b, float c, float d) {
+  const uint32_t h0 = pack_bf16x2(a, b), h1 = pack_bf16x2(c, d);
+  *reinterpret_cast<uint2*>(hi) = make_uint2(h0, h1);
+  *reinterpret_cast<uint2*>(hi + PLANE_LO) =
+      make_uint2(pack_bf16x2(a - __uint_as_float(h0 << 16), b - __uint_as_float(h0 & 0xffff0000u)),
+                 pack_bf16x2(c - __uint_as_float(h1 << 16), d - __uint_as_float(h1 & 0xffff0000u)));
+}
+
 // Eight consecutive elements of a weight (or KV) row, as raw registers until converted.
 template <typename T> struct Vec8;
 template <> struct Vec8<bf16_t> {

@@ -15,8 +15,31 @@ namespace {
 constexpr int GV_WAVES = 4;
 constexpr int GV_LDS_FLOATS = 36864;    // 144 KB of staged input rows per block (160 KB LDS)
 
+// The epilogue of a kernel instance: an EPI_* value fixed at compile time (with no branch on it ahead
+// of the first loads, those go out in one burst instead of waiting for the branches' arguments in
+// turn), or GV_ANY: a.epi.
+constexpr int GV_ANY = -1;
+template <int KIND>
+__device__ __forceinline__ bool epi_is(const LinearArgs& a, int epi) {
+  return KIND == GV_ANY ? a.epi == epi : KIND == epi;
+}
+template <int KIND>
+__device__ __forceinline__ bool epi_gated(const LinearArgs& a) {
+  return epi_is<KIND>(a, EPI_GATED_GELU) || epi_is<KIND>(a, EPI_GATED_SILU);
+}
+
 __device__ __forceinline__ float apply_epi_act(int epi, float g, float u) {
   return (epi == EPI_GATED_GELU ? gelu_tanh(g) : silu(g)) * u;
+}
+
+// One of the three matrix pointers.  Held in scalar registers first: left to itself the compiler turns
+// the choice into an address in the argument buffer and loads the pointer from there, a memory round
+// trip ahead of the weights (the cast through the global address space keeps the loads global).
+__device__ __forceinline__ const void* pick_matrix(const LinearArgs& a, int mat) {
+  uint64_t p0 = (uint64_t)a.w[0], p1 = (uint64_t)a.w[1], p2 = (uint64_t)a.w[2];
+  asm("" : "+s"(p0), "+s"(p1), "+s"(p2));
+  const uint64_t p = mat == 0 ? p0 : (mat == 1 ? p1 : p2);
+  return (const void*)(const __attribute__((address_space(1))) void*)p;
 }
 
 // Weight rows of one wave's current row pair: two consecutive rows of one of the concatenated
@@ -29,11 +52,11 @@ struct RowPair {
   bool ok0, ok1;
 };
 
-template <typename WT>
-__device__ __forceinline__ RowPair<WT> row_pair(const LinearArgs& a, bool gated, int n_total, int pr) {
+template <typename WT, int KIND>
+__device__ __forceinline__ RowPair<WT> row_pair(const LinearArgs& a, int n_total, int pr) {
   RowPair<WT> r;
   const int K = a.K;
-  if (gated) {
+  if (epi_gated<KIND>(a)) {
     r.ok0 = r.ok1 = pr < a.n_per;
     const int q = r.ok0 ? pr : 0;
     r.n0 = r.n1 = pr;
@@ -41,20 +64,17 @@ __device__ __forceinline__ RowPair<WT> row_pair(const LinearArgs& a, bool gated,
     r.w1 = reinterpret_cast<const WT*>(a.w[1]) + (size_t)q * K;
     return r;
   }
-  if (a.epi == EPI_QKV) {
-    // the pair (i, i + d_head/2) of one head of one matrix: the rotary pair
-    const int hd2 = a.n_per >> 1, half = a.d_head >> 1;
+  if (epi_is<KIND>(a, EPI_QKV)) {
+    // the pair (i, i + d_head/2) of one head of one matrix: the rotary pair (d_head is 64 or 128)
+    const int hd2 = a.n_per >> 1, half = a.d_head >> 1, sh = __builtin_ctz(half);
     r.ok0 = r.ok1 = pr < 3 * hd2;
     const int q = r.ok0 ? pr : 0;
     const int mat = q >= hd2 ? (q >= 2 * hd2 ? 2 : 1) : 0;
-    const int loc = q - mat * hd2;
-    const int h = loc / half, i = loc - h * half;
+    const int loc = q - mat * hd2, h = loc >> sh, i = loc & (half - 1);
     const int c0 = h * a.d_head + i;
     r.n0 = mat * a.n_per + c0;
     r.n1 = r.n0 + half;
-    // select among the three matrix pointers (an indexed a.w[mat] would be fetched from the
-    // argument buffer by a vector load, making the weight loads wait for the inputs)
-    const void* base = mat == 0 ? a.w[0] : (mat == 1 ? a.w[1] : a.w[2]);
+    const void* base = pick_matrix(a, mat);
     r.w0 = reinterpret_cast<const WT*>(base) + (size_t)c0 * K;
     r.w1 = r.w0 + (size_t)half * K;
     return r;
@@ -63,14 +83,9 @@ __device__ __forceinline__ RowPair<WT> row_pair(const LinearArgs& a, bool gated,
   r.n1 = 2 * pr + 1;
   r.ok0 = r.n0 < n_total;
   r.ok1 = r.n1 < n_total;
-  int v0 = r.ok0 ? r.n0 : 0, v1 = r.ok1 ? r.n1 : v0;
-  // locate each virtual row in its matrix without a division (at most three matrices)
-  const void* b0 = a.w[0];
-  if (v0 >= a.n_per) { v0 -= a.n_per; b0 = a.w[1]; if (v0 >= a.n_per) { v0 -= a.n_per; b0 = a.w[2]; } }
-  const void* b1 = a.w[0];
-  if (v1 >= a.n_per) { v1 -= a.n_per; b1 = a.w[1]; if (v1 >= a.n_per) { v1 -= a.n_per; b1 = a.w[2]; } }
-  r.w0 = reinterpret_cast<const WT*>(b0) + (size_t)v0 * K;
-  r.w1 = reinterpret_cast<const WT*>(b1) + (size_t)v1 * K;
+  const int v0 = r.ok0 ? r.n0 : 0, v1 = r.ok1 ? r.n1 : v0;  // one matrix
+  r.w0 = reinterpret_cast<const WT*>(a.w[0]) + (size_t)v0 * K;
+  r.w1 = reinterpret_cast<const WT*>(a.w[0]) + (size_t)v1 * K;
   return r;
 }
 
@@ -221,13 +236,14 @@ __device__ __forceinline__ void fma_pieces(const Vec8<WT> (&buf)[2][GV_KP], cons
 // wave's two outputs per row (already scaled by 1/rms when folded), yold the residual values
 // lane 0 read before the weights.  Argmax partials are merged over the block's waves (one
 // barrier; every thread of the block must call this).
-template <typename WT, int MB>
+template <typename WT, int MB, int KIND>
 __device__ __forceinline__ void gemv_finish(const LinearArgs& a, const RowPair<WT>& r,
                                             const float (&acc)[2][MB], const float (&yold)[2][MB],
-                                            bool live, bool gated, bool argmax, int m0, int mrows,
+                                            bool live, int m0, int mrows,
                                             int tid, int lane, int wave, float (&rv)[GV_WAVES][MB],
                                             int (&ri)[GV_WAVES][MB], const QkvPre& pre = {},
                                             bool use_pre = false) {
+  const bool gated = epi_gated<KIND>(a), argmax = epi_is<KIND>(a, EPI_ARGMAX);
   float best_v[MB];
   int best_i[MB];
 #pragma unroll
@@ -248,7 +264,7 @@ __device__ __forceinline__ void gemv_finish(const LinearArgs& a, const RowPair<W
         }
       }
     }
-  } else if (lane == 0 && live && a.epi == EPI_QKV) {
+  } else if (lane == 0 && live && epi_is<KIND>(a, EPI_QKV)) {
     if (use_pre) {
       const int HD = a.n_per, mat = r.n0 >= HD ? (r.n0 >= 2 * HD ? 2 : 1) : 0;
       qkv_store_pre(a, mat, r.n0 - mat * HD, m0, pre, acc[0][0], acc[1][0]);
@@ -261,7 +277,7 @@ __device__ __forceinline__ void gemv_finish(const LinearArgs& a, const RowPair<W
       if (m >= mrows) break;
       const size_t row = (size_t)(m0 + m);
       if (gated) {
-        if (r.ok0) a.y[row * a.ldy + r.n0] = apply_epi_act(a.epi, acc[0][m], acc[1][m]);
+        if (r.ok0) a.y[row * a.ldy + r.n0] = apply_epi_act(KIND == GV_ANY ? a.epi : KIND, acc[0][m], acc[1][m]);
         continue;
       }
 #pragma unroll
@@ -271,15 +287,15 @@ __device__ __forceinline__ void gemv_finish(const LinearArgs& a, const RowPair<W
         const int n = s ? r.n1 : r.n0;
         const float v = acc[s][m];
         float* yp = a.y + row * a.ldy + n;
-        if (a.epi == EPI_STORE) {
+        if (epi_is<KIND>(a, EPI_STORE)) {
           *yp = v;
-        } else if (a.epi == EPI_RESID) {
+        } else if (epi_is<KIND>(a, EPI_RESID)) {
           const float t = yold[s][m] + v;
           *yp = t;
           if (a.stash) a.stash[row * a.lds + n] = t;
-        } else if (a.epi == EPI_BIAS_GELU) {
+        } else if (epi_is<KIND>(a, EPI_BIAS_GELU)) {
           *yp = gelu_tanh(v + a.bias[n]);
-        } else if (a.epi == EPI_BIAS_RESID) {
+        } else if (epi_is<KIND>(a, EPI_BIAS_RESID)) {
           *yp = yold[s][m] + (v + (a.bias ? a.bias[n] : 0.f));
         }
       }

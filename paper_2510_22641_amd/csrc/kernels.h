@@ -80,38 +80,29 @@ struct LinearArgs {
   const float* rope_cos = nullptr;  // [max_seq][d_head/2] or null (no rotation)
   const float* rope_sin = nullptr;
   int32_t* status = nullptr;        // SSD_DEV_CAPACITY / SSD_DEV_BAD_PAGE bits
-  // row statistics for the MFMA path's normalisation (filled by launch_linear)
-  float2* stats = nullptr;    // [M] workspace
-  int use_mfma = -1;          // -1: choose; 0: vector path; 1: MFMA path
-  // Skinny path operands, in buffers of plane_rows rows (a multiple of 16, >= M).  Input: bf16
-  // planes hi / lo of the (gain-multiplied) rows, hi row m at in_planes + m * in_ld, lo row m at
-  // in_planes + (plane_rows + m) * in_ld; with NORM_RMS, 1/rms of row m comes from the partial sums
-  // of squares in_ssq[p * plane_rows + m], p < in_nssq.
-  int plane_rows = 16;
+  // Row-plane operands (2 rows and more, bf16 weights): hi / lo bf16 planes of the
+  // (gain-multiplied) rows in fragment order (plane_at in device.h) over row_groups = ceil(M / 16)
+  // groups; with NORM_RMS, 1/rms of row m comes from the partial sums of squares
+  // in_ssq[p * 16 row_groups + m], p < in_nssq.
+  int row_groups = 1;  // set by the launchers
   const bf16_t* in_planes = nullptr;
-  int in_ld = 0;
   const float* in_ssq = nullptr;
   int in_nssq = 0;
-  // launch_linear_skinny_fold with NORM_SOFTMAX: float32 input rows (row m at in_f32 + m * in_ld)
+  // launch_fold_rows with NORM_SOFTMAX: float32 input rows (row m at in_f32 + m * in_ld)
   // turned into softmax probabilities over groups of `group` consecutive inputs.
   const float* in_f32 = nullptr;
-  // Output planes for the next skinny launch (EPI_RESID: of out_gain * y_new, plus per-block
-  // partial sums of squares of y_new in out_ssq[block * plane_rows + m]; gated: of y; null: none).
+  int in_ld = 0;
+  // Output planes for the next launch (EPI_RESID: of out_gain * y_new, plus per-block partial sums
+  // of squares of y_new in out_ssq[block * 16 row_groups + m]; gated and bias + GELU: of y; null: none).
   bf16_t* out_planes = nullptr;
-  int out_ld = 0;
   float* out_ssq = nullptr;
   const float* out_gain = nullptr;
-  // Tile path (rows past the skinny capacity): a buffer for the bf16 hi / lo planes of the
-  // (gain-multiplied) input rows, gemm_plane_rows rows of at most gemm_plane_ld elements per
-  // plane; null keeps the tile kernels that split the inputs themselves.
-  bf16_t* gemm_planes = nullptr;
-  int gemm_plane_rows = 0;
-  int gemm_plane_ld = 0;
-  // Tile path, residual projections (y += W . x): partial products over ranges of K, float32
-  // [kpart_max][gemm_plane_rows][kpart_ld], which a second launch adds to y in range order; null
-  // keeps one pass over K.  ksplit is set by the launcher.
+  // Long row blocks, residual projections (y += W . x): partial products over ranges of K, float32
+  // [kpart_max][kpart_rows][kpart_ld], which a second launch adds to y in range order; null keeps
+  // one pass over K.  ksplit is set by the launcher.
   float* kpart = nullptr;
   int kpart_max = 0;
+  int kpart_rows = 0;
   int kpart_ld = 0;
   int ksplit = 1;
 };
@@ -129,6 +120,9 @@ struct LaunchTiming {
   bool timed = false;
 };
 
+// Compute units of the current device.
+int cu_count();
+
 // Pieces per batch (the KP of gemv_kernel) the vector path uses for rows of K elements.
 int gemv_pieces(int K);
 
@@ -137,43 +131,41 @@ int gemv_pieces(int K);
 hipError_t launch_linear(LinearArgs a, hipStream_t s, int* n_parts = nullptr,
                          LaunchTiming* timing = nullptr);
 
+// One input row (M == 1): launches it and sets *taken when its size and input transform fit the one-row
+// kernels.
+hipError_t launch_one_row(const LinearArgs& a, hipStream_t s, LaunchTiming* timing, bool* taken);
+
 // Two one-row GEMVs that read the same inputs, in one launch (the blocks of `a` first, then those
-// of `b`): `a` with bf16 weights and K <= 2048, `b` with float32 weights and K <= 4096, no input
-// transform, store / residual / bias epilogues only.
+// of `b`): `a` with bf16 weights, K <= 2048 and the bias / residual epilogue, `b` with float32
+// weights, K <= 4096 and a store; no input transform.
 bool linear_pair_ok(const LinearArgs& a, const LinearArgs& b);
 hipError_t launch_linear_pair(const LinearArgs& a, const LinearArgs& b, hipStream_t s);
 
 // Upper bound of the partials per row for n_out outputs (workspace sizing).
 int argmax_parts_max(int n_out);
 
-// Rows of a verify chunk (2..128, bf16 weights) take the skinny MFMA path (16 rows per block
-// row of the grid): the inputs arrive as bf16 planes written once by their producer (a.in_planes
-// ..., see LinearArgs), with RMSNorm folded (a.norm = NORM_RMS: the gain is already in the planes,
-// 1/rms from a.in_ssq) or none; the gated, QKV (rotary + KV store), residual (+ next planes), bias
-// and argmax epilogues.
-bool skinny_ok(int M, int K, int wdtype);
-hipError_t launch_linear_skinny(const LinearArgs& a, hipStream_t s, int* n_parts = nullptr);
+// Two rows and more with bf16 weights: the inputs arrive as bf16 planes written once by their
+// producer (a.in_planes ..., see LinearArgs), with RMSNorm folded (a.norm = NORM_RMS: the gain is
+// already in the planes, 1/rms from a.in_ssq) or none; the store, gated (to planes), QKV (rotary +
+// KV store), residual (+ next planes), bias and argmax epilogues.  K is a multiple of 64.
+// *n_parts: argmax partials per row; *n_ssq: partial sums of squares a residual epilogue leaves.
+hipError_t launch_linear_rows(const LinearArgs& a, hipStream_t s, int* n_parts = nullptr,
+                              int* n_ssq = nullptr);
+// Planes of gain * x for M rows and, when ssq is set, the full-row sums of squares ssq[m] (one
+// partial): the input of the first launch of a pass.  With shift: planes of the LayerNorm
+// (x - mean) / sqrt(var + eps) * gain + shift.
+hipError_t launch_rows_prep(const float* x, int ldx, int M, int K, const float* gain,
+                            const float* shift, float eps, bf16_t* out, float* ssq, hipStream_t s);
+// Floats of partial sums of squares the residual launches of d_model features over up to `rows`
+// rows may leave.
+size_t rows_ssq_floats(int d_model, int rows);
 
-// Planes of gain * x for M <= plane_rows rows (hi row m at out + m * ldo, lo at
-// out + (plane_rows + m) * ldo) and the full-row sums of squares ssq[m] (one partial): the input
-// of the first skinny launch of a pass.
-hipError_t launch_skinny_prep(const float* x, int ldx, int M, int K, const float* gain,
-                              bf16_t* out, int ldo, int plane_rows, float* ssq, hipStream_t s);
-
-// 16-feature tiles of a skinny launch.
-int skinny_blocks(int n_out);
-// The folded cross-attention of a verify chunk (at most 8 rows, float32 weights) on half tiles:
-// the scores fold_q . rms(x) (NORM_RMS, EPI_STORE, input planes as launch_linear_skinny's) or the
-// output y += fold_o . softmax(scores) per group (NORM_SOFTMAX, EPI_RESID, float32 input rows
-// in_f32).  skinny_fold_ok tells whether a chunk of M rows with these sizes takes this path.
-bool skinny_fold_ok(int d_model, int n_fold, int group, int M);
-hipError_t launch_linear_skinny_fold(const LinearArgs& a, hipStream_t s);
-// Partial sums of squares a skinny residual epilogue of n_out features over M rows leaves (the
-// in_nssq of its consumer): one per tile, or two with half tiles.
-int skinny_ssq_parts(int n_out, int M);
-
-// True when launch_linear takes the weight-streaming vector path (the one that has EPI_QKV).
-bool linear_is_vector(const LinearArgs& a);
+// The folded cross-attention of a verify chunk (2..8 rows, float32 weights): the scores
+// fold_q . rms(x) (NORM_RMS, EPI_STORE, input planes as launch_linear_rows') or the output
+// y += fold_o . softmax(scores) per group (NORM_SOFTMAX, EPI_RESID, float32 input rows in_f32).
+// fold_rows_ok tells whether a chunk of M rows with these sizes takes this path.
+bool fold_rows_ok(int d_model, int n_fold, int group, int M);
+hipError_t launch_fold_rows(const LinearArgs& a, hipStream_t s, int* n_ssq = nullptr);
 
 // Algorithmic HBM bytes of a launch: weights + input rows + output rows (+ residual reads).
 double linear_bytes(const LinearArgs& a);
@@ -197,27 +189,12 @@ struct EmbedArgs {
 };
 hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
 
-// q/k/v rows (qkv [R][3*HD], R = B*C) -> rotary (LLaMA) -> q_out [R][HD], K/V into the pools.
-struct RopeScatterArgs {
-  const float* qkv;
-  float* q_out;
-  int B, C, H, dh;
-  int kvdtype;
-  PagedKV kv;
-  const float* rope_cos;  // [max_seq][dh/2] or null (no rotation)
-  const float* rope_sin;
-  int max_seq;
-  int32_t* status;
-};
-hipError_t launch_rope_scatter(const RopeScatterArgs& a, hipStream_t s);
-
 constexpr int ATTN_SPLITS_MAX = 8;
 
 struct AttnArgs {
   const float* q;  // [B*C][H*dh]
-  float* out;      // [B*C][H*dh]
-  bf16_t* out_planes = nullptr;  // optional hi / lo bf16 planes of out (lo plane_rows rows on)
-  int plane_rows = 16;
+  float* out;      // [B*C][H*dh], or null when out_planes is set
+  bf16_t* out_planes = nullptr;  // optional hi / lo planes of out, fragment order
   // key-split partials (long contexts): [part_rows][H][ATTN_SPLITS_MAX][dh + 2] floats, or null
   float* part = nullptr;
   int part_rows = 0;
@@ -252,10 +229,6 @@ hipError_t launch_cross_fold(const void* xk, const void* xv, int kvdtype, const 
 // wdtype.
 hipError_t launch_fold_fg(const float* fold_q, const float* gain, const void* wo, int wdtype,
                           int HN, int d, int HD, float* fg, hipStream_t s);
-
-// Row statistics for normalisation: stats[m] = (mean, 1/sqrt(var+eps)) (LN) or (0, 1/rms) (RMS).
-hipError_t launch_row_stats(const float* x, int ldx, int M, int K, int norm, float eps,
-                            float2* stats, hipStream_t s);
 
 // Confidence-stopped drafting, evaluated by the final argmax of draft step `step` (row m =
 // sequence m): conf = the row's largest softmax probability, 1 / sum_n exp(logits[n] - max),

@@ -1,4 +1,4 @@
-// Small kernels of the decode loop: input gather, rotary + KV scatter, argmax reduction, greedy
+// Small kernels of the decode loop: input gather, argmax reduction, greedy
 // acceptance with KV-length rollback, and generation bookkeeping.
 #include "device.h"
 #include "kernels.h"
@@ -26,78 +26,50 @@ __global__ void embed_kernel(const EmbedArgs a) {
     }
     src = reinterpret_cast<const WT*>(a.embed) + (size_t)tok * a.d;
   }
-  for (int k = threadIdx.x; k < a.d; k += blockDim.x) xr[k] = load_elem(src + k);
+  if ((uintptr_t)src & 15) {  // the caller's table or visual rows are not aligned for vector loads
+    for (int k = threadIdx.x; k < a.d; k += blockDim.x) xr[k] = load_elem(src + k);
+    return;
+  }
+  for (int k = threadIdx.x * 8; k < a.d; k += blockDim.x * 8) {  // d is a multiple of 64
+    Vec8<WT> v;
+    v.load(src + k);
+    float f[8];
+    v.to_f32(f);
+    *reinterpret_cast<float4*>(xr + k) = make_float4(f[0], f[1], f[2], f[3]);
+    *reinterpret_cast<float4*>(xr + k + 4) = make_float4(f[4], f[5], f[6], f[7]);
+  }
 }
 
-template <typename KT>
-__global__ void rope_scatter_kernel(const RopeScatterArgs a) {
-  const int r = blockIdx.x;
-  const int b = r / a.C, j = r - b * a.C;
-  const int HD = a.H * a.dh, half = a.dh / 2;
-  const int pos = a.kv.seq_len[b] + a.kv.pos_off + j;
-  int page = -1;
-  const int pg_i = pos >= 0 ? pos / a.kv.page_size : -1;
-  if (pos < 0 || pos >= a.max_seq || pg_i >= a.kv.max_pages) {
-    if (threadIdx.x == 0) atomicOr(a.status, SSD_DEV_CAPACITY);
-  } else {
-    page = a.kv.page_table[(size_t)b * a.kv.max_pages + pg_i];
-    if (page < 0 || page >= a.kv.n_pages) {
-      if (threadIdx.x == 0) atomicOr(a.status, SSD_DEV_BAD_PAGE);
-      page = -1;
-    }
-  }
-  const int slot = pos - pg_i * a.kv.page_size;
-  const int tpos = pos < 0 ? 0 : (pos >= a.max_seq ? a.max_seq - 1 : pos);
-  const float* src = a.qkv + (size_t)r * 3 * HD;
-  for (int idx = threadIdx.x; idx < a.H * half; idx += blockDim.x) {
-    const int h = idx / half, i = idx - h * half;
-    const int c0 = h * a.dh + i, c1 = c0 + half;
-    float q0 = src[c0], q1 = src[c1];
-    float k0 = src[HD + c0], k1 = src[HD + c1];
-    const float v0 = src[2 * HD + c0], v1 = src[2 * HD + c1];
-    if (a.rope_cos) {
-      const float cs = a.rope_cos[(size_t)tpos * half + i], sn = a.rope_sin[(size_t)tpos * half + i];
-      const float rq0 = q0 * cs - q1 * sn, rq1 = q1 * cs + q0 * sn;
-      const float rk0 = k0 * cs - k1 * sn, rk1 = k1 * cs + k0 * sn;
-      q0 = rq0; q1 = rq1; k0 = rk0; k1 = rk1;
-    }
-    a.q_out[(size_t)r * HD + c0] = q0;
-    a.q_out[(size_t)r * HD + c1] = q1;
-    if (page >= 0) {
-      const size_t off = (((size_t)page * a.H + h) * a.kv.page_size + slot) * a.dh;
-      KT* kp = reinterpret_cast<KT*>(a.kv.k) + off;
-      KT* vp = reinterpret_cast<KT*>(a.kv.v) + off;
-      store_elem(kp + i, k0);
-      store_elem(kp + i + half, k1);
-      store_elem(vp + i, v0);
-      store_elem(vp + i + half, v1);
-    }
-  }
-}
+// One block of 16 waves per row: with four waves a LM head of 32128 features left 16 dependent rounds
+// of partials per thread (7.8 us a launch; 16 waves take them in one).
+constexpr int AF_THREADS = 1024;
 
 template <typename WT>
-__global__ __launch_bounds__(256) void argmax_final_kernel(const float* pv, const int* pi, int M,
+__global__ __launch_bounds__(AF_THREADS) void argmax_final_kernel(const float* pv, const int* pi, int M,
                                                            int n_parts, int C, int32_t* dst0,
                                                            int ld0, int off0, int32_t* dst1,
                                                            const WT* embed, int d, float* x_out,
                                                            const ConfArgs cf) {
-  constexpr int PER = 16;  // partials per thread requested together
-  __shared__ float sv[4];
-  __shared__ int si[4];
+  constexpr int PER = 4, NW = AF_THREADS / 64;  // partials per thread requested together
+  __shared__ float sv[NW];
+  __shared__ int si[NW];
   __shared__ int tok;
   __shared__ float vmax;
   const int m = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float v = -INFINITY;
   int i = INT_MAX;
-  for (int p0 = 0; p0 < n_parts; p0 += 256 * PER) {
+  const float* pr = pv + (size_t)m * n_parts;
+  const int* ir = pi + (size_t)m * n_parts;
+  for (int p0 = 0; p0 < n_parts; p0 += AF_THREADS * PER) {
     float vv[PER];
     int ii[PER];
+    // (a partial past the last repeats it: the maximum is the same)
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int p = p0 + u * 256 + threadIdx.x;
-      vv[u] = p < n_parts ? pv[(size_t)m * n_parts + p] : -INFINITY;
-      ii[u] = p < n_parts ? pi[(size_t)m * n_parts + p] : INT_MAX;
+      const int p = min(p0 + u * AF_THREADS + (int)threadIdx.x, n_parts - 1);
+      vv[u] = pr[p];
+      ii[u] = ir[p];
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) argmax_merge(v, i, vv[u], ii[u]);
@@ -105,14 +77,18 @@ __global__ __launch_bounds__(256) void argmax_final_kernel(const float* pv, cons
   wave_argmax(v, i);
   if (lane == 0) { sv[wave] = v; si[wave] = i; }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) argmax_merge(v, i, sv[w], si[w]);
-    if (i == INT_MAX) i = 0;  // every logit NaN: nothing sensible to choose
-    const int b = m / C, j = m - b * C;
-    dst0[(size_t)b * ld0 + off0 + j] = i;
-    if (dst1) dst1[m] = i;
-    tok = i;
-    vmax = v;
+  if (wave == 0) {
+    v = sv[lane & (NW - 1)];
+    i = si[lane & (NW - 1)];
+    wave_argmax(v, i);
+    if (lane == 0) {
+      if (i == INT_MAX) i = 0;  // every logit NaN: nothing sensible to choose
+      const int b = m / C, j = m - b * C;
+      dst0[(size_t)b * ld0 + off0 + j] = i;
+      if (dst1) dst1[m] = i;
+      tok = i;
+      vmax = v;
+    }
   }
   if (cf.logits) {
     // confidence: 1 / sum_n exp(logit_n - max) over the row
@@ -326,13 +302,6 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_rope_scatter(const RopeScatterArgs& a, hipStream_t s) {
-  if (a.B * a.C <= 0) return hipSuccess;
-  if (a.kvdtype == 1) hipLaunchKernelGGL(rope_scatter_kernel<bf16_t>, dim3(a.B * a.C), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(rope_scatter_kernel<float>, dim3(a.B * a.C), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_argmax_final_ex(const float* part_val, const int* part_idx, int M, int n_parts,
                                   int C, int32_t* dst0, int ld0, int off0, int32_t* dst1,
                                   const void* embed, int wdtype, int d, float* x_out,
@@ -341,11 +310,11 @@ hipError_t launch_argmax_final_ex(const float* part_val, const int* part_idx, in
   if (x_out && (!embed || d < 1)) return hipErrorInvalidValue;
   if (cf.logits && (!cf.drafting || !cf.ndraft || cf.V < 1)) return hipErrorInvalidValue;
   if (x_out && wdtype == 1)
-    hipLaunchKernelGGL(argmax_final_kernel<bf16_t>, dim3(M), dim3(256), 0, s, part_val, part_idx,
+    hipLaunchKernelGGL(argmax_final_kernel<bf16_t>, dim3(M), dim3(AF_THREADS), 0, s, part_val, part_idx,
                        M, n_parts, C, dst0, ld0, off0, dst1,
                        reinterpret_cast<const bf16_t*>(embed), d, x_out, cf);
   else
-    hipLaunchKernelGGL(argmax_final_kernel<float>, dim3(M), dim3(256), 0, s, part_val, part_idx,
+    hipLaunchKernelGGL(argmax_final_kernel<float>, dim3(M), dim3(AF_THREADS), 0, s, part_val, part_idx,
                        M, n_parts, C, dst0, ld0, off0, dst1,
                        x_out ? reinterpret_cast<const float*>(embed) : nullptr, d, x_out, cf);
   return hipGetLastError();

@@ -33,14 +33,13 @@ int t5_bucket(int n, int buckets, int max_dist) {
 }
 
 struct Layout {
-  size_t x, x1, qkv, q, attn, ffn, inh, xi, stash, vis, part_val, part_idx, stats, bias_tab,
-      p_x, p_attn, p_ffn, ssq, attn_part, fold_q, fold_o,
+  size_t x, x1, q, attn, ffn, inh, xi, stash, vis, part_val, part_idx, bias_tab,
+      p_x, p_attn, p_ffn, p_inh, ssq, attn_part, fold_q, fold_o,
       bucket, rope_cos, rope_sin, status, cur_tok, g_pending, g_draft, g_target,
-      g_count, g_active, g_nactive, g_stats, g_ndraft, g_drafting, g_draft_w, conf_lg, gplanes,
+      g_count, g_active, g_nactive, g_stats, g_ndraft, g_drafting, g_draft_w, conf_lg,
       fold_fg, kpart, total;
   int rows_max, head_rows, parts_max, ctx_max, plane_rows, attn_rows;
-  int gplane_rows = 0, gplane_ld = 0;  // tile-path input planes (0 rows: none)
-  int kpart_max = 0;                   // K-range partials of the tile path's residual projections
+  int kpart_max = 0;  // K-range partials of the long row blocks' residual projections
   bool fold = false;  // the folded cross-attention matrices are carved (fold_q, fold_o)
   bool fg = false;    // and the scores-from-the-layer-input matrices of layers 1..k (fold_fg)
 };
@@ -83,53 +82,38 @@ bool make_layout(const ssd_dims& d, Layout& L, bool allow_fold = true) {
   L.rows_max = (int)rows;
   L.head_rows = (int)(B * (G + 1));
   L.parts_max = argmax_parts_max(d.vocab);
-  // bf16 hi / lo operand planes of the skinny MFMA path (plane_rows rows each: the largest verify
-  // chunk, rounded up to 16, at most 128) and its partial sums of squares
-  {
-    size_t pr = B * (G + 1);
-    // (T5: the visual rows too, so the prefill's cross K/V projections take the skinny path)
-    if (d.arch == SSD_ARCH_T5 && B * (size_t)d.n_visual <= 128 && B * (size_t)d.n_visual > pr)
-      pr = B * (size_t)d.n_visual;
-    pr = pr < 16 ? 16 : (pr > 128 ? 128 : (pr + 15) / 16 * 16);
-    L.plane_rows = (int)pr;
-  }
+  // bf16 weights: passes of two rows and more hand their activations on as bf16 hi / lo planes
+  // (plane_rows rows each) with partial sums of squares; single rows, and float32 weights, as
+  // float32 rows
+  const bool bf16 = d.wdtype == SSD_BF16;
+  L.plane_rows = (int)((rows + 15) / 16 * 16);
   // key-split partials of the long-context attention (up to 16 query rows per sequence)
   L.attn_rows = (int)(B * 16);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-  auto lane = [&](Layout& X, size_t R, size_t head_rows) {
-    const size_t PRz = (size_t)L.plane_rows;
-    X.x = take(R * D * 4);
-    X.x1 = take((B * D + HD) * 4);  // room for a one-row attention output right after the row
-    X.qkv = take(R * 3 * HD * 4);
-    X.q = take(R * HD * 4);
-    X.attn = take(R * HD * 4);
-    X.ffn = take(R * (size_t)d.d_ff * 4);
-    X.inh = take(B * (size_t)d.in_hidden * 4);
-    X.xi = take(B * D * 4);
-    X.stash = take(B * (G + 1) * D * 4);
-    X.part_val = take(head_rows * L.parts_max * 4);
-    X.part_idx = take(head_rows * L.parts_max * 4);
-    X.stats = take(R * 8);
-    X.p_x = take(2 * PRz * D * 2);
-    X.p_attn = take(2 * PRz * HD * 2);
-    X.p_ffn = take(2 * PRz * (size_t)d.d_ff * 2);
-    X.ssq = take((size_t)2 * skinny_blocks((int)D) * PRz * 4);  // up to two partials per tile
-    X.attn_part = take((size_t)L.attn_rows * d.n_heads * ATTN_SPLITS_MAX * (d.d_head + 2) * 4);
-    X.cur_tok = take(B * 4);
-  };
-  lane(L, rows, (size_t)L.head_rows);
-  // bf16 hi / lo planes of a context block's input rows for the tile GEMM (prefill)
   {
-    int ld = (int)D;
-    if ((int)HD > ld) ld = (int)HD;
-    if (d.d_ff > ld) ld = d.d_ff;
-    L.gplane_ld = (ld + 7) / 8 * 8;
-    L.gplane_rows = (int)rows;
-    L.gplanes = take((size_t)2 * rows * L.gplane_ld * 2);
-    // contexts beyond the skinny capacity and one 128-row tile: room for four K-range partials
-    L.kpart_max = (rows > (size_t)L.plane_rows && rows > 128) ? 4 : 0;
-    L.kpart = take((size_t)L.kpart_max * rows * D * 4);
+    const size_t R = rows, PR = bf16 ? (size_t)L.plane_rows : 0, head_rows = (size_t)L.head_rows;
+    const size_t R1 = bf16 ? 1 : R;  // float32 rows of what the planes replace
+    L.x = take(R * D * 4);
+    L.x1 = take((B * D + HD) * 4);  // room for a one-row attention output right after the row
+    L.q = take(R * HD * 4);
+    L.attn = take(R1 * HD * 4);
+    L.ffn = take(R1 * (size_t)d.d_ff * 4);
+    L.inh = take(B * (size_t)d.in_hidden * 4);
+    L.xi = take(B * D * 4);
+    L.stash = take(B * (G + 1) * D * 4);
+    L.part_val = take(head_rows * L.parts_max * 4);
+    L.part_idx = take(head_rows * L.parts_max * 4);
+    L.p_x = take(2 * PR * D * 2);
+    L.p_attn = take(2 * PR * HD * 2);
+    L.p_ffn = take(2 * PR * (size_t)d.d_ff * 2);
+    L.p_inh = take(bf16 ? 2 * ((B + 15) / 16 * 16) * (size_t)d.in_hidden * 2 : 0);
+    L.ssq = take(bf16 ? rows_ssq_floats((int)D, (int)R) * 4 : 0);
+    L.attn_part = take((size_t)L.attn_rows * d.n_heads * ATTN_SPLITS_MAX * (d.d_head + 2) * 4);
+    L.cur_tok = take(B * 4);
+    // row blocks past 128 rows: room for four K-range partials of the residual projections
+    L.kpart_max = bf16 && R > 128 ? 4 : 0;
+    L.kpart = take((size_t)L.kpart_max * R * D * 4);
   }
   L.vis = take(d.arch == SSD_ARCH_T5 ? B * (size_t)d.n_visual * D * 4 : 0);
   {
@@ -297,16 +281,11 @@ hipError_t run_linear(ssd_ctx* c, const LinearArgs& a, int* n_parts = nullptr) {
 LinearArgs lin(ssd_ctx* c) {
   LinearArgs a;
   a.wdtype = c->d.wdtype;
-  a.stats = c->at<float2>(c->L.stats);
-  if (c->L.gplane_rows > 0) {
-    a.gemm_planes = c->at<bf16_t>(c->L.gplanes);
-    a.gemm_plane_rows = c->L.gplane_rows;
-    a.gemm_plane_ld = c->L.gplane_ld;
-    if (c->L.kpart_max > 0) {
-      a.kpart = c->at<float>(c->L.kpart);
-      a.kpart_max = c->L.kpart_max;
-      a.kpart_ld = (int)c->d.d_model;
-    }
+  if (c->L.kpart_max > 0) {
+    a.kpart = c->at<float>(c->L.kpart);
+    a.kpart_max = c->L.kpart_max;
+    a.kpart_rows = c->L.rows_max;
+    a.kpart_ld = c->d.d_model;
   }
   a.eps = c->d.norm_eps;
   return a;
@@ -320,38 +299,33 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
   hipStream_t s = c->stream;
   const int R = B * C, D = d.d_model, HD = d.n_heads * d.d_head;
   const bool t5 = d.arch == SSD_ARCH_T5;
-  // 2..16 rows in bf16: MFMA with operands written once as bf16 (the verify chunk)
-  const int PR = c->L.plane_rows;
-  const bool skinny = R <= PR && skinny_ok(R, D, d.wdtype) && skinny_ok(R, HD, d.wdtype) &&
-                      skinny_ok(R, d.d_ff, d.wdtype);
-  float* qkv = c->at<float>(c->L.qkv);
+  // two rows and more with bf16 weights: MFMA with operands written once as bf16 planes
+  const bool planes = R >= 2 && d.wdtype == SSD_BF16;
   float* q = c->at<float>(c->L.q);
   float* attn = c->at<float>(c->L.attn);
   float* ffn = c->at<float>(c->L.ffn);
   int32_t* status = c->at<int32_t>(c->L.status);
-  // skinny operands: bf16 planes written once by each producer (p_x: gain * residual for the
-  // RMS-normalised projections, with per-block sums of squares in ssq; p_attn, p_ffn)
+  // plane operands, written once by each producer (p_x: gain * residual for the RMS-normalised
+  // projections, with per-block sums of squares in ssq; p_attn, p_ffn)
   bf16_t* p_x = c->at<bf16_t>(c->L.p_x);
   bf16_t* p_attn = c->at<bf16_t>(c->L.p_attn);
   bf16_t* p_ffn = c->at<bf16_t>(c->L.p_ffn);
   float* ssq = c->at<float>(c->L.ssq);
-  const int nssq_resid = skinny_ssq_parts(D, R);
   int nssq = 1;  // partials behind the current p_x
-  // one linear layer: the skinny MFMA path for a verify chunk, else the vector / tile paths
-  auto linear = [&](LinearArgs& a, const bf16_t* in, int in_ld) -> hipError_t {
-    if (!skinny) return run_linear(c, a);
+  // one linear layer: the plane path, else the vector path on float32 rows
+  auto linear = [&](LinearArgs& a, const bf16_t* in) -> hipError_t {
+    if (!planes) return run_linear(c, a);
     a.in_planes = in;
-    a.in_ld = in_ld;
-    a.plane_rows = PR;
     if (a.norm == NORM_RMS) { a.in_ssq = ssq; a.in_nssq = nssq; }
-    return launch_linear_skinny(a, s);
+    return launch_linear_rows(a, s, nullptr, a.out_ssq ? &nssq : nullptr);
   };
   // a residual projection also leaves the planes of gain_next * x for the next projection
   auto resid_out = [&](LinearArgs& a, const float* gain_next) {
-    if (!skinny || !gain_next) return;
-    a.out_planes = p_x; a.out_ld = D; a.out_ssq = ssq; a.out_gain = gain_next;
+    if (!planes || !gain_next) return;
+    a.out_planes = p_x; a.out_ssq = ssq; a.out_gain = gain_next;
   };
-  if (skinny) HIP_TRY(launch_skinny_prep(x, D, R, D, c->layers[l0].attn_norm, p_x, D, PR, ssq, s));
+  if (planes)
+    HIP_TRY(launch_rows_prep(x, D, R, D, c->layers[l0].attn_norm, nullptr, 0.f, p_x, ssq, s));
   for (int l = l0; l < l1; ++l) {
     const ssd_layer_weights& lw = c->layers[l];
     // self-attention
@@ -364,25 +338,13 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
     a.kvdtype = d.kvdtype; a.max_seq = d.max_seq; a.status = status;
     a.rope_cos = t5 ? nullptr : c->at<float>(c->L.rope_cos);
     a.rope_sin = t5 ? nullptr : c->at<float>(c->L.rope_sin);
-    if (skinny || linear_is_vector(a)) {
-      // rotary and the KV store fused into the projection's epilogue
-      HIP_TRY(linear(a, p_x, D));
-    } else {
-      a.epi = EPI_STORE; a.y = qkv; a.ldy = 3 * HD;
-      HIP_TRY(run_linear(c, a));
-      RopeScatterArgs rs;
-      rs.qkv = qkv; rs.q_out = q; rs.B = B; rs.C = C; rs.H = d.n_heads; rs.dh = d.d_head;
-      rs.kvdtype = d.kvdtype; rs.kv = a.kv;
-      rs.rope_cos = a.rope_cos; rs.rope_sin = a.rope_sin;
-      rs.max_seq = d.max_seq; rs.status = status;
-      HIP_TRY(launch_rope_scatter(rs, s));
-    }
+    // rotary and the KV store fused into the projection's epilogue
+    HIP_TRY(linear(a, p_x));
     // one-row steps of layers 1..k with fold_fg: the attention output goes right after the
     // residual row, so that [x; o] is one input row of the folded-scores GEMV
     const bool fg = t5 && c->fg_ready && R == 1 && l < d.draft_layers;
     AttnArgs at;
-    at.q = q; at.out = fg ? x + D : attn; at.out_planes = skinny ? p_attn : nullptr;
-    at.plane_rows = PR;
+    at.q = q; at.out = planes ? nullptr : (fg ? x + D : attn); at.out_planes = planes ? p_attn : nullptr;
     at.part = c->at<float>(c->L.attn_part); at.part_rows = c->L.attn_rows;
     at.B = B; at.C = C; at.H = d.n_heads; at.dh = d.d_head;
     at.kvdtype = d.kvdtype; at.cross = 0; at.kv = paged(c, l, pos_off);
@@ -416,8 +378,7 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
     a.x = attn; a.ldx = HD; a.M = R; a.K = HD;
     a.w[0] = lw.wo; a.n_per = D; a.epi = EPI_RESID; a.y = x; a.ldy = D;
     resid_out(a, t5 ? lw.xattn_norm : lw.ffn_norm);
-    HIP_TRY(linear(a, p_attn, HD));
-    nssq = nssq_resid;
+    HIP_TRY(linear(a, p_attn));
     // cross-attention to the visual tokens
     if (t5 && c->fold_ready && R == 1) {
       // folded: scores = fold_q . rmsnorm(x), then x += fold_o . softmax(scores) per head
@@ -434,8 +395,8 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
       a.w[0] = c->at<float>(c->L.fold_o) + (size_t)l * c->fold_layer_elems(); a.wdtype = SSD_F32;
       a.n_per = D; a.epi = EPI_RESID; a.y = x; a.ldy = D;
       HIP_TRY(run_linear(c, a));
-    } else if (t5 && skinny && c->fold_ready &&
-               skinny_fold_ok(D, d.n_heads * d.n_visual, d.n_visual, R)) {
+    } else if (t5 && planes && c->fold_ready &&
+               fold_rows_ok(D, d.n_heads * d.n_visual, d.n_visual, R)) {
       // folded, for a verify chunk on half tiles (float32 matrices split into bf16 hi / lo in the
       // kernel): scores = fold_q . rmsnorm(x) per row, then x += fold_o . softmax(scores) per head
       // with the softmax taken in the second launch's input loads
@@ -445,22 +406,22 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
       a.norm = NORM_RMS; a.gain = lw.xattn_norm;
       a.w[0] = c->at<float>(c->L.fold_q) + (size_t)l * c->fold_layer_elems(); a.wdtype = SSD_F32;
       a.n_per = HN; a.epi = EPI_STORE; a.y = q; a.ldy = HD;
-      a.in_planes = p_x; a.in_ld = D; a.plane_rows = PR; a.in_ssq = ssq; a.in_nssq = nssq;
-      HIP_TRY(launch_linear_skinny_fold(a, s));
+      a.in_planes = p_x; a.in_ssq = ssq; a.in_nssq = nssq;
+      HIP_TRY(launch_fold_rows(a, s));
       a = lin(c);
       a.x = q; a.ldx = HD; a.M = R; a.K = HN;
       a.norm = NORM_SOFTMAX; a.group = d.n_visual;
       a.w[0] = c->at<float>(c->L.fold_o) + (size_t)l * c->fold_layer_elems(); a.wdtype = SSD_F32;
       a.n_per = D; a.epi = EPI_RESID; a.y = x; a.ldy = D;
-      a.in_f32 = q; a.in_ld = HD; a.plane_rows = PR;
+      a.in_f32 = q; a.in_ld = HD;
       resid_out(a, lw.ffn_norm);
-      HIP_TRY(launch_linear_skinny_fold(a, s));
+      HIP_TRY(launch_fold_rows(a, s, &nssq));
     } else if (t5) {
       a = lin(c);
       a.x = x; a.ldx = D; a.M = R; a.K = D;
       a.norm = NORM_RMS; a.gain = lw.xattn_norm;
       a.w[0] = lw.xq; a.n_per = HD; a.epi = EPI_STORE; a.y = q; a.ldy = HD;
-      HIP_TRY(linear(a, p_x, D));
+      HIP_TRY(linear(a, p_x));
       AttnArgs xa = at;
       xa.cross = 1;
       xa.bias = nullptr;
@@ -473,7 +434,7 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
       a.x = attn; a.ldx = HD; a.M = R; a.K = HD;
       a.w[0] = lw.xo; a.n_per = D; a.epi = EPI_RESID; a.y = x; a.ldy = D;
       resid_out(a, lw.ffn_norm);
-      HIP_TRY(linear(a, p_attn, HD));
+      HIP_TRY(linear(a, p_attn));
     }
     }
     // feed-forward
@@ -482,14 +443,14 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
     a.norm = NORM_RMS; a.gain = lw.ffn_norm;
     a.w[0] = lw.w_gate; a.w[1] = lw.w_up; a.n_mats = 2; a.n_per = d.d_ff;
     a.epi = t5 ? EPI_GATED_GELU : EPI_GATED_SILU; a.y = ffn; a.ldy = d.d_ff;
-    if (skinny) { a.y = nullptr; a.out_planes = p_ffn; a.out_ld = d.d_ff; }
-    HIP_TRY(linear(a, p_x, D));
+    if (planes) { a.y = nullptr; a.out_planes = p_ffn; }
+    HIP_TRY(linear(a, p_x));
     a = lin(c);
     a.x = ffn; a.ldx = d.d_ff; a.M = R; a.K = d.d_ff;
     a.w[0] = lw.w_down; a.n_per = D; a.epi = EPI_RESID; a.y = x; a.ldy = D;
     if (stash && l == stash_layer) { a.stash = stash; a.lds = ld_stash; }
     resid_out(a, l + 1 < l1 ? c->layers[l + 1].attn_norm : nullptr);
-    HIP_TRY(linear(a, p_ffn, d.d_ff));
+    HIP_TRY(linear(a, p_ffn));
   }
   return SSD_OK;
 }
@@ -511,14 +472,13 @@ int run_head(ssd_ctx* c, const float* x, int ldx, int M, int C, float* logits, i
   a.part_idx = c->at<int>(c->L.part_idx);
   a.logits = logits; a.ldl = ldl;
   int n_parts = 0;
-  if (M <= c->L.plane_rows && skinny_ok(M, d.d_model, d.wdtype)) {
+  if (M >= 2 && d.wdtype == SSD_BF16) {
     bf16_t* p_x = c->at<bf16_t>(c->L.p_x);
     float* ssq = c->at<float>(c->L.ssq);
-    const int PR = c->L.plane_rows;
-    HIP_TRY(launch_skinny_prep(x, ldx, M, d.d_model, c->w.final_norm, p_x, d.d_model, PR, ssq,
-                               c->stream));
-    a.in_planes = p_x; a.in_ld = d.d_model; a.in_ssq = ssq; a.in_nssq = 1; a.plane_rows = PR;
-    HIP_TRY(launch_linear_skinny(a, c->stream, &n_parts));
+    HIP_TRY(launch_rows_prep(x, ldx, M, d.d_model, c->w.final_norm, nullptr, 0.f, p_x, ssq,
+                             c->stream));
+    a.in_planes = p_x; a.in_ssq = ssq; a.in_nssq = 1;
+    HIP_TRY(launch_linear_rows(a, c->stream, &n_parts));
   } else {
     HIP_TRY(run_linear(c, a, &n_parts));
   }
@@ -551,13 +511,28 @@ int run_imitation(ssd_ctx* c, const float* xk, int B, F between) {
   a.norm = NORM_LN; a.gain = c->w.in_ln_w; a.shift = c->w.in_ln_b; a.eps = d.ln_eps;
   a.w[0] = c->w.in_w1; a.n_per = d.in_hidden; a.epi = EPI_BIAS_GELU; a.bias = c->w.in_b1;
   a.y = inh; a.ldy = d.in_hidden;
-  HIP_TRY(run_linear(c, a));
+  // more than 8 rows with bf16 weights: on planes of the normalised rows and of the hidden features
+  const bool planes = B > 8 && d.wdtype == SSD_BF16;
+  bf16_t* p_inh = c->at<bf16_t>(c->L.p_inh);
+  if (planes) {
+    bf16_t* p_x = c->at<bf16_t>(c->L.p_x);
+    HIP_TRY(launch_rows_prep(xk, D, B, D, a.gain, a.shift, a.eps, p_x, nullptr, c->stream));
+    a.norm = NORM_NONE; a.in_planes = p_x; a.out_planes = p_inh;
+    HIP_TRY(launch_linear_rows(a, c->stream));
+  } else {
+    HIP_TRY(run_linear(c, a));
+  }
   HIP_TRY(between());
   a = lin(c);
   a.x = inh; a.ldx = d.in_hidden; a.M = B; a.K = d.in_hidden;
   a.w[0] = c->w.in_w2; a.n_per = D; a.epi = EPI_BIAS_RESID; a.bias = c->w.in_b2;
   a.resid = d.in_residual ? xk : nullptr; a.ldr = D; a.y = c->at<float>(c->L.xi); a.ldy = D;
-  HIP_TRY(run_linear(c, a));
+  if (planes) {
+    a.in_planes = p_inh;
+    HIP_TRY(launch_linear_rows(a, c->stream));
+  } else {
+    HIP_TRY(run_linear(c, a));
+  }
   return SSD_OK;
 }
 
@@ -966,22 +941,22 @@ int ssd_prefill(ssd_ctx* c, int B, int P, const int32_t* d_prompt, const void* d
     ev.wdtype = d.wdtype; ev.t0 = nullptr; ev.t1 = nullptr; ev.ld1 = 0;
     ev.visual = d_visual; ev.n_visual = d.n_visual; ev.n_prefix = d.n_visual; ev.status = status;
     HIP_TRY(launch_embed(ev, s));
-    float* tmp = c->at<float>(c->L.qkv);
-    // the visual rows as skinny operand planes once for all 2L projections, when they fit
-    const int MV = B * d.n_visual, PR = c->L.plane_rows;
-    const bool sk = MV <= PR && skinny_ok(MV, D, d.wdtype) && skinny_ok(MV, HD, d.wdtype);
+    float* tmp = c->at<float>(c->L.q);
+    // the visual rows as operand planes once for all 2L projections
+    const int MV = B * d.n_visual;
+    const bool planes = MV >= 2 && d.wdtype == SSD_BF16;
     bf16_t* p_x = c->at<bf16_t>(c->L.p_x);
-    if (sk)
-      HIP_TRY(launch_skinny_prep(vis, D, MV, D, nullptr, p_x, D, PR, c->at<float>(c->L.ssq), s));
+    if (planes)
+      HIP_TRY(launch_rows_prep(vis, D, MV, D, nullptr, nullptr, 0.f, p_x, nullptr, s));
     for (int l = 0; l < d.n_layers; ++l) {
       for (int which = 0; which < 2; ++which) {
         LinearArgs a = lin(c);
         a.x = vis; a.ldx = D; a.M = MV; a.K = D;
         a.w[0] = which ? c->layers[l].xv : c->layers[l].xk; a.n_per = HD;
         a.epi = EPI_STORE; a.y = tmp; a.ldy = HD;
-        if (sk) {
-          a.in_planes = p_x; a.in_ld = D; a.plane_rows = PR;
-          HIP_TRY(launch_linear_skinny(a, s));
+        if (planes) {
+          a.in_planes = p_x;
+          HIP_TRY(launch_linear_rows(a, s));
         } else {
           HIP_TRY(run_linear(c, a));
         }
