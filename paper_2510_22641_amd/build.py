@@ -22,7 +22,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssd.so")
 SOURCES = ["linear.hip", "gemv1.hip", "gemm.hip", "gemm_rows_store.hip", "gemm_rows_store_rms.hip",
            "gemm_rows_resid.hip", "gemm_rows_qkv.hip", "gemm_rows_gated.hip",
-           "gemm_rows_argmax.hip", "attention.hip", "misc.hip", "sample.hip", "ssd_api.hip"]
+           "gemm_rows_argmax.hip", "gemm_rows_cross.hip",
+           "attention.hip", "misc.hip", "sample.hip", "ssd_api.hip"]
 ARCH = "gfx950"
 
 

@@ -1113,9 +1113,13 @@ hipError_t launch_attn_t(const AttnArgs& a, hipStream_t s) {
 // (one 16-byte load of Wq per e) and wave w the keys j = w, w + 4, ... (the four waves read the
 // same weights, from L2 after the first); the head's keys sit in LDS.
 template <typename KT, typename WT, int NV>
-__global__ __launch_bounds__(256) void fold_q_kernel(const KT* __restrict__ xk,
-                                                     const WT* __restrict__ wq, float* __restrict__ fq,
-                                                     int dh, int d) {
+__global__ __launch_bounds__(256) void fold_q_kernel(const KT* __restrict__ xk, size_t kv_stride,
+                                                     const void* const* __restrict__ wqs,
+                                                     float* __restrict__ fq, int dh, int d) {
+  const int layer = blockIdx.z, H = gridDim.y;
+  const WT* __restrict__ wq = reinterpret_cast<const WT*>(wqs[layer]);
+  xk += (size_t)layer * kv_stride;
+  fq += (size_t)layer * H * NV * d;
   constexpr int JW = (NV + 3) / 4;  // keys per wave
   __shared__ __attribute__((aligned(16))) float ks[NV][128 + 4];
   const int h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1164,9 +1168,13 @@ __global__ __launch_bounds__(256) void fold_q_kernel(const KT* __restrict__ xk,
 // Block (row tile, head h): thread t owns output row n and reads its dh weights of head h (a
 // contiguous run, eight elements per load); the head's values sit in LDS, read four e at a time.
 template <typename KT, typename WT, int NV>
-__global__ __launch_bounds__(256) void fold_o_kernel(const KT* __restrict__ xv,
-                                                     const WT* __restrict__ wo, float* __restrict__ fo,
-                                                     int H, int dh, int d) {
+__global__ __launch_bounds__(256) void fold_o_kernel(const KT* __restrict__ xv, size_t kv_stride,
+                                                     const void* const* __restrict__ wos,
+                                                     float* __restrict__ fo, int H, int dh, int d) {
+  const int layer = blockIdx.z;
+  const WT* __restrict__ wo = reinterpret_cast<const WT*>(wos[layer]);
+  xv += (size_t)layer * kv_stride;
+  fo += (size_t)layer * H * NV * d;
   __shared__ __attribute__((aligned(16))) float vs[NV][128 + 4];
   const int h = blockIdx.y, n = blockIdx.x * 256 + threadIdx.x;
   for (int i = threadIdx.x; i < NV * dh; i += 256) {
@@ -1211,27 +1219,27 @@ __global__ __launch_bounds__(256) void fold_o_kernel(const KT* __restrict__ xv,
 }
 
 template <typename KT, typename WT, int NV>
-hipError_t launch_fold_t(const void* xk, const void* xv, const void* wq, const void* wo, int H,
-                         int dh, int d, float* fq, float* fo, hipStream_t s) {
-  const dim3 grid((d + 255) / 256, H);
-  hipLaunchKernelGGL((fold_q_kernel<KT, WT, NV>), dim3((d + 511) / 512, H), dim3(256), 0, s,
-                     reinterpret_cast<const KT*>(xk), reinterpret_cast<const WT*>(wq), fq, dh, d);
+hipError_t launch_fold_t(const void* xk, const void* xv, size_t kv_stride, const void* const* wq,
+                         const void* const* wo, int L, int H, int dh, int d, float* fq, float* fo,
+                         hipStream_t s) {
+  hipLaunchKernelGGL((fold_q_kernel<KT, WT, NV>), dim3((d + 511) / 512, H, L), dim3(256), 0, s,
+                     reinterpret_cast<const KT*>(xk), kv_stride, wq, fq, dh, d);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((fold_o_kernel<KT, WT, NV>), grid, dim3(256), 0, s,
-                     reinterpret_cast<const KT*>(xv), reinterpret_cast<const WT*>(wo), fo, H, dh, d);
+  hipLaunchKernelGGL((fold_o_kernel<KT, WT, NV>), dim3((d + 255) / 256, H, L), dim3(256), 0, s,
+                     reinterpret_cast<const KT*>(xv), kv_stride, wo, fo, H, dh, d);
   return hipGetLastError();
 }
 
 template <int NV>
-hipError_t launch_fold_nv(const void* xk, const void* xv, int kvdtype, const void* wq,
-                          const void* wo, int wdtype, int H, int dh, int d, float* fq, float* fo,
-                          hipStream_t s) {
+hipError_t launch_fold_nv(const void* xk, const void* xv, size_t st, int kvdtype, const void* const* wq,
+                          const void* const* wo, int wdtype, int L, int H, int dh, int d, float* fq,
+                          float* fo, hipStream_t s) {
   if (kvdtype == 1)
-    return wdtype == 1 ? launch_fold_t<bf16_t, bf16_t, NV>(xk, xv, wq, wo, H, dh, d, fq, fo, s)
-                       : launch_fold_t<bf16_t, float, NV>(xk, xv, wq, wo, H, dh, d, fq, fo, s);
-  return wdtype == 1 ? launch_fold_t<float, bf16_t, NV>(xk, xv, wq, wo, H, dh, d, fq, fo, s)
-                     : launch_fold_t<float, float, NV>(xk, xv, wq, wo, H, dh, d, fq, fo, s);
+    return wdtype == 1 ? launch_fold_t<bf16_t, bf16_t, NV>(xk, xv, st, wq, wo, L, H, dh, d, fq, fo, s)
+                       : launch_fold_t<bf16_t, float, NV>(xk, xv, st, wq, wo, L, H, dh, d, fq, fo, s);
+  return wdtype == 1 ? launch_fold_t<float, bf16_t, NV>(xk, xv, st, wq, wo, L, H, dh, d, fq, fo, s)
+                     : launch_fold_t<float, float, NV>(xk, xv, st, wq, wo, L, H, dh, d, fq, fo, s);
 }
 
 }  // namespace
@@ -1286,9 +1294,14 @@ __device__ __forceinline__ void fg_load(FgRegs<WT>& r, const float* __restrict__
 
 template <typename WT>
 __global__ __launch_bounds__(256) void fold_fg_kernel(const float* __restrict__ fq,
-                                                      const float* __restrict__ g,
-                                                      const WT* __restrict__ wo, int HN, int d,
-                                                      int HD, float* __restrict__ fg) {
+                                                      const float* const* __restrict__ gs,
+                                                      const void* const* __restrict__ wos, int HN,
+                                                      int d, int HD, float* __restrict__ fg) {
+  const int layer = blockIdx.z;
+  const float* __restrict__ g = gs[layer];
+  const WT* __restrict__ wo = reinterpret_cast<const WT*>(wos[layer]);
+  fq += (size_t)layer * HN * d;
+  fg += (size_t)layer * HN * (d + HD);
   constexpr int KS = 64, LDK = KS + 8;  // K per step; bf16 per LDS row (with padding)
   __shared__ __attribute__((aligned(16))) bf16_t Ah[64 * LDK], Al[64 * LDK], Bt[64 * LDK];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1362,28 +1375,27 @@ bool cross_fold_ok(int nv, int dh) {
   return (nv == 8 || nv == 16 || nv == 32 || nv == 64) && dh <= 128;
 }
 
-hipError_t launch_fold_fg(const float* fold_q, const float* gain, const void* wo, int wdtype,
-                          int HN, int d, int HD, float* fg, hipStream_t s) {
-  if (HN < 1 || d < 1 || HD < 1) return hipErrorInvalidValue;
-  dim3 grid((HD + 63) / 64, (HN + 63) / 64);
+hipError_t launch_fold_fg(const float* fold_q, const float* const* gain, const void* const* wo,
+                          int wdtype, int n_layers, int HN, int d, int HD, float* fg, hipStream_t s) {
+  if (HN < 1 || d < 1 || HD < 1 || n_layers < 1) return hipErrorInvalidValue;
+  dim3 grid((HD + 63) / 64, (HN + 63) / 64, n_layers);
   if (wdtype == 1)
-    hipLaunchKernelGGL(fold_fg_kernel<bf16_t>, grid, dim3(256), 0, s, fold_q, gain,
-                       reinterpret_cast<const bf16_t*>(wo), HN, d, HD, fg);
+    hipLaunchKernelGGL(fold_fg_kernel<bf16_t>, grid, dim3(256), 0, s, fold_q, gain, wo, HN, d, HD, fg);
   else
-    hipLaunchKernelGGL(fold_fg_kernel<float>, grid, dim3(256), 0, s, fold_q, gain,
-                       reinterpret_cast<const float*>(wo), HN, d, HD, fg);
+    hipLaunchKernelGGL(fold_fg_kernel<float>, grid, dim3(256), 0, s, fold_q, gain, wo, HN, d, HD, fg);
   return hipGetLastError();
 }
 
-hipError_t launch_cross_fold(const void* xk, const void* xv, int kvdtype, const void* wq,
-                             const void* wo, int wdtype, int H, int nv, int dh, int d, float* fq,
-                             float* fo, hipStream_t s) {
-  if (!cross_fold_ok(nv, dh) || H < 1 || d < 1 || d % 8) return hipErrorInvalidValue;
+hipError_t launch_cross_fold(const void* xk, const void* xv, size_t kv_stride, int kvdtype,
+                             const void* const* wq, const void* const* wo, int wdtype, int n_layers,
+                             int H, int nv, int dh, int d, float* fq, float* fo, hipStream_t s) {
+  if (!cross_fold_ok(nv, dh) || H < 1 || d < 1 || d % 8 || n_layers < 1) return hipErrorInvalidValue;
+  const size_t st = kv_stride;
   switch (nv) {
-    case 8: return launch_fold_nv<8>(xk, xv, kvdtype, wq, wo, wdtype, H, dh, d, fq, fo, s);
-    case 16: return launch_fold_nv<16>(xk, xv, kvdtype, wq, wo, wdtype, H, dh, d, fq, fo, s);
-    case 32: return launch_fold_nv<32>(xk, xv, kvdtype, wq, wo, wdtype, H, dh, d, fq, fo, s);
-    default: return launch_fold_nv<64>(xk, xv, kvdtype, wq, wo, wdtype, H, dh, d, fq, fo, s);
+    case 8: return launch_fold_nv<8>(xk, xv, st, kvdtype, wq, wo, wdtype, n_layers, H, dh, d, fq, fo, s);
+    case 16: return launch_fold_nv<16>(xk, xv, st, kvdtype, wq, wo, wdtype, n_layers, H, dh, d, fq, fo, s);
+    case 32: return launch_fold_nv<32>(xk, xv, st, kvdtype, wq, wo, wdtype, n_layers, H, dh, d, fq, fo, s);
+    default: return launch_fold_nv<64>(xk, xv, st, kvdtype, wq, wo, wdtype, n_layers, H, dh, d, fq, fo, s);
   }
 }
 

@@ -166,7 +166,7 @@ __device__ __forceinline__ void qkv_pair_tile(const LinearArgs& a, int u, int& m
 template <int MI, int NJ, int KB, int NS>
 constexpr int ring_lds() { return NS * KB * (4 * MI + 2 * NJ) * 1024; }
 
-enum RingKind { RING_PLAIN = 0, RING_GATED = 1, RING_QKV = 2 };
+enum RingKind { RING_PLAIN = 0, RING_GATED = 1, RING_QKV = 2, RING_CROSS = 3 };
 
 template <int KIND, int MI, int NJ, int KB, int NS>
 __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
   }
   const int m0 = rt * BM;
   int nk = K / RK, kb = 0;
-  if (a.ksplit > 1) {  // K range zs of a.ksplit (whole steps each)
+  if (KIND != RING_CROSS && a.ksplit > 1) {  // K range zs of a.ksplit (whole steps each)
     const int per = (nk + a.ksplit - 1) / a.ksplit;
     kb = zs * per;
     nk = min(per, nk - kb);
@@ -244,7 +244,8 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
         row0 = min(ct * BN + n, n_out - 1);
         row = min(ct * BN + n + prow, n_out - 1);
       }
-      src[q] = reinterpret_cast<const char*>(mat_ptr(a, mat) + (size_t)row0 * K + (size_t)kb * RK);
+      const bf16_t* wm = KIND == RING_CROSS ? reinterpret_cast<const bf16_t*>(a.wtab[zs]) : mat_ptr(a, mat);
+      src[q] = reinterpret_cast<const char*>(wm + (size_t)row0 * K + (size_t)kb * RK);
       off[q] = (uint32_t)(row - row0) * (uint32_t)K * 2u + pch * 16u;
     }
   }
@@ -394,6 +395,16 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = acc[j][i][e] * rsc;
       if (!rok || n >= n_out) continue;
+      if constexpr (KIND == RING_CROSS) {  // matrix zs of the table
+        const size_t o = cross_at(a, zs >> 1, m, n);
+        void* dst = zs & 1 ? a.cross_v : a.cross_k;
+        if (a.kvdtype == 1)
+          *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(dst) + o) =
+              make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        else
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(dst) + o) = make_float4(v[0], v[1], v[2], v[3]);
+        continue;
+      }
       if (a.ksplit > 1) {
         *reinterpret_cast<float4*>(a.kpart + ((size_t)zs * a.kpart_rows + m) * a.kpart_ld + n) =
             make_float4(v[0], v[1], v[2], v[3]);
@@ -537,7 +548,7 @@ hipError_t launch_ring_t(const LinearArgs& a, int n_out, hipStream_t s) {
     }
   }
   const int width = KIND == RING_GATED ? 2 * n_out : n_out;
-  const dim3 grid((a.M + 32 * MI - 1) / (32 * MI), (width + 32 * NJ - 1) / (32 * NJ), a.ksplit);
+  const dim3 grid((a.M + 32 * MI - 1) / (32 * MI), (width + 32 * NJ - 1) / (32 * NJ), KIND == RING_CROSS ? a.n_tab : a.ksplit);
   hipLaunchKernelGGL((gemm_ring_kernel<KIND, MI, NJ, KB, NS>), grid, dim3(256), shm, s, a);
   return hipGetLastError();
 }
@@ -582,16 +593,21 @@ hipError_t launch_linear_rows(const LinearArgs& args, hipStream_t s, int* n_part
   if (a.epi == EPI_QKV ? a.n_mats != 3 || (a.d_head != 64 && a.d_head != 128) : !gated && a.n_mats != 1)
     return hipErrorInvalidValue;
   const int n_out = gated ? a.n_per : a.n_per * a.n_mats;
+  const bool cross = a.epi == EPI_CROSS;
+  if (cross && (!a.wtab || a.n_tab < 1 || a.norm != NORM_NONE || a.n_visual < 1 || (a.d_head != 64 && a.d_head != 128) ||
+                n_out != a.n_heads * a.d_head || !a.cross_k || !a.cross_v))
+    return hipErrorInvalidValue;
   LinearArgs b = a;
   b.ksplit = 1;
   if (a.M <= ROWS_MAX) {
-    const RowsShape sh = rows_shape(n_out, a.M, a.epi);
+    const RowsShape sh = rows_shape(cross ? n_out * a.n_tab : n_out, a.M, a.epi);
     const int tf = gated || sh.mode == GR_HALF ? 8 : 16;
     const int blocks = ((n_out + tf - 1) / tf + sh.nt - 1) / sh.nt;
     if (b.epi == EPI_ARGMAX) b.n_parts = blocks;
     if (n_parts) *n_parts = b.n_parts;
     if (n_ssq) *n_ssq = blocks;
     const bool rms = b.norm == NORM_RMS;
+    if (cross) return launch_rows_cross(b, sh, blocks, s);
     if (b.epi == EPI_STORE) return rms ? launch_rows_store_rms(b, sh, blocks, s) : launch_rows_store(b, sh, blocks, s);
     if (rms != (gated || b.epi == EPI_QKV || b.epi == EPI_ARGMAX)) return hipErrorInvalidValue;
     if (b.epi == EPI_RESID) return launch_rows_resid(b, sh, blocks, s);
@@ -603,7 +619,7 @@ hipError_t launch_linear_rows(const LinearArgs& args, hipStream_t s, int* n_part
   const bool vec = b.epi == EPI_ARGMAX || (n_out % 8 == 0 && b.n_per % 4 == 0);
   if (!vec) return hipErrorInvalidValue;
   const bool split = b.epi == EPI_RESID && b.kpart && n_out <= b.kpart_ld;
-  const RingShape sh = ring_shape(n_out, a.M, a.K, gated, split, a.kpart_max);
+  const RingShape sh = ring_shape(cross ? n_out * a.n_tab : n_out, a.M, a.K, gated, split, a.kpart_max);
   b.ksplit = sh.ksplit;
   const int cols = ((gated ? 2 * n_out : n_out) + 32 * sh.nj - 1) / (32 * sh.nj);
   if (b.epi == EPI_ARGMAX) b.n_parts = 2 * cols;
@@ -611,7 +627,8 @@ hipError_t launch_linear_rows(const LinearArgs& args, hipStream_t s, int* n_part
   const int slices = (n_out + KSUM_COLS - 1) / KSUM_COLS;
   if (n_ssq) *n_ssq = sh.ksplit > 1 ? slices : 2 * cols;
   hipError_t e = gated ? launch_ring<RING_GATED>(b, sh, n_out, s)
-                       : (b.epi == EPI_QKV ? launch_ring<RING_QKV>(b, sh, n_out, s)
+                       : (cross ? launch_ring<RING_CROSS>(b, sh, n_out, s)
+                       : b.epi == EPI_QKV ? launch_ring<RING_QKV>(b, sh, n_out, s)
                                            : launch_ring<RING_PLAIN>(b, sh, n_out, s));
   if (e != hipSuccess || sh.ksplit == 1) return e;
   hipLaunchKernelGGL(ksum_rows_kernel, dim3(a.row_groups, slices), dim3(256), 0, s, b, n_out);

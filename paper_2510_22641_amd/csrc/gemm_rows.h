@@ -20,12 +20,19 @@ hipError_t launch_rows_store_rms(const LinearArgs& a, RowsShape sh, int blocks, 
 hipError_t launch_rows_resid(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 hipError_t launch_rows_qkv(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 hipError_t launch_rows_gated(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
+hipError_t launch_rows_cross(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 hipError_t launch_rows_argmax(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 
 namespace {
 
 __device__ __forceinline__ const bf16_t* mat_ptr(const LinearArgs& a, int mat) {
   return reinterpret_cast<const bf16_t*>(pick_matrix(a, mat));
+}
+
+// Element of the cross-attention caches: row m = b Nv + n, feature f = h dh + e of layer l.
+__device__ __forceinline__ size_t cross_at(const LinearArgs& a, int l, int m, int f) {
+  const int b = m / a.n_visual, n = m - b * a.n_visual, sh = __builtin_ctz(a.d_head), h = f >> sh;
+  return ((((size_t)l * a.cross_batch + b) * a.n_heads + h) * a.n_visual + n) * a.d_head + (f - (h << sh));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -66,7 +73,7 @@ constexpr int gr_one(int mode, int nt, int rg) {
 
 // The epilogue is a template parameter: with no branch on it ahead of the first loads, every load
 // of the prologue goes out in one burst instead of waiting for the branches' arguments in turn.
-enum GrKind { GR_STORE = 0, GR_STORE_RMS, GR_RESID, GR_QKV, GR_GATED, GR_ARGMAX };
+enum GrKind { GR_STORE = 0, GR_STORE_RMS, GR_RESID, GR_QKV, GR_GATED, GR_ARGMAX, GR_CROSS };
 
 // ONE: a wave's share of K fits one batch (everything it reads is in flight at once).  ONCE: one row
 // block, so each weight is read by one block only and need not stay in the caches (at 12 rows of the
@@ -93,7 +100,9 @@ __global__ __launch_bounds__(64 * GR_WAVES) void gemv_rows_kernel(const LinearAr
   const int n_out = qkv ? 3 * a.n_per : a.n_per;
   constexpr int tf = gated ? 8 : TF;           // features a tile
   const int tiles = (n_out + tf - 1) / tf;
-  const int by = blockIdx.y, bx = blockIdx.z * 8 + blockIdx.x;
+  // GR_CROSS: matrix mtx of the table
+  const int mtx = KIND == GR_CROSS ? blockIdx.z / a.tab_z : 0;
+  const int by = blockIdx.y, bx = (blockIdx.z - mtx * a.tab_z) * 8 + blockIdx.x;
   const int t0 = by * ROWS, j0 = bx * NT;
   if (j0 >= tiles) return;  // the whole block
 
@@ -106,6 +115,7 @@ __global__ __launch_bounds__(64 * GR_WAVES) void gemv_rows_kernel(const LinearAr
   };
   // this lane's weight row of each piece: row lane / 8, elements 8 (lane % 8) .. of a step
   const bf16_t* wrow[NT][WL];
+  const bf16_t* w0 = reinterpret_cast<const bf16_t*>(KIND == GR_CROSS ? a.wtab[mtx] : a.w[0]);
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -119,7 +129,7 @@ __global__ __launch_bounds__(64 * GR_WAVES) void gemv_rows_kernel(const LinearAr
       } else if (gated) {
         p = mat_ptr(a, hf) + (size_t)min(vt * 8 + r, a.n_per - 1) * K;
       } else {
-        p = mat_ptr(a, 0) + (size_t)min(vt * TF + 8 * hf + r, n_out - 1) * K;
+        p = w0 + (size_t)min(vt * TF + 8 * hf + r, n_out - 1) * K;
       }
       wrow[j][hf] = p + (lane & 7) * 8;
     }
@@ -360,6 +370,13 @@ __global__ __launch_bounds__(64 * GR_WAVES) void gemv_rows_kernel(const LinearAr
         if (a.logits) a.logits[(size_t)tg * a.ldl + n] = v;
         continue;
       }
+      if constexpr (KIND == GR_CROSS) {
+        const size_t o = cross_at(a, mtx >> 1, tg, n);
+        void* dst = mtx & 1 ? a.cross_v : a.cross_k;
+        if (a.kvdtype == 1) store_elem(reinterpret_cast<bf16_t*>(dst) + o, v);
+        else store_elem(reinterpret_cast<float*>(dst) + o, v);
+        continue;
+      }
       float* yp = a.y + (size_t)tg * a.ldy + n;
       if (resid) {
         const float t = (pre ? y_old[i] : *yp) + v;
@@ -411,8 +428,10 @@ hipError_t launch_rows_u(const LinearArgs& a, int blocks, hipStream_t s) {
     }
   }
   // workgroups go to the 8 XCDs by linear id: x is the XCD
-  const dim3 grid(8, (a.M + 16 * RG - 1) / (16 * RG), (blocks + 7) / 8);
-  hipLaunchKernelGGL((gemv_rows_kernel<KIND, MODE, NT, RG, U, ONE, ONCE>), grid, dim3(64 * GR_WAVES), shm, s, a);
+  LinearArgs b = a;
+  b.tab_z = (blocks + 7) / 8;
+  const dim3 grid(8, (a.M + 16 * RG - 1) / (16 * RG), b.tab_z * (KIND == GR_CROSS ? a.n_tab : 1));
+  hipLaunchKernelGGL((gemv_rows_kernel<KIND, MODE, NT, RG, U, ONE, ONCE>), grid, dim3(64 * GR_WAVES), shm, s, b);
   return hipGetLastError();
 }
 
@@ -423,7 +442,7 @@ template <int KIND, int MODE, int NT, int RG>
 hipError_t launch_rows_t(const LinearArgs& a, int blocks, hipStream_t s) {
   constexpr int one = gr_one(MODE, NT, RG), u = gr_batch(MODE, NT, RG);
   const int row_blocks = (a.M + 16 * RG - 1) / (16 * RG);
-  if ((long long)blocks * row_blocks <= cu_count()) {
+  if (KIND != GR_CROSS && (long long)blocks * row_blocks <= cu_count()) {
     const int per_wave = (a.K / 64 + GR_WAVES - 1) / GR_WAVES;
     if constexpr (one >= 2) if (per_wave <= 2) return launch_rows_u<KIND, MODE, NT, RG, 2, true, MODE != GR_FULL>(a, blocks, s);
     if constexpr (one >= 4) if (per_wave <= 4) return launch_rows_u<KIND, MODE, NT, RG, 4, true, MODE != GR_FULL>(a, blocks, s);

@@ -35,6 +35,9 @@ enum Epi {
   EPI_BIAS_GELU = 4,   // y[m][n] = gelu_tanh(acc + bias[n])
   EPI_BIAS_RESID = 5,  // y[m][n] = (resid ? resid[m][n] : 0) + acc + (bias ? bias[n] : 0)
   EPI_ARGMAX = 6,      // per-block (max, argmax) over n for each m; logits[m][n] = acc if wanted
+  EPI_CROSS = 8,       // a table of matrices (wtab) over the same rows, m = b*Nv + n: the cross-attention
+                       // keys (even entries) and values (odd) of every layer into their caches
+                       // (launch_linear_rows only)
   EPI_QKV = 7          // w = (wq, wk, wv): rotary on q and k (when rope_cos is set), q -> y[m][.],
                        // k and v into the paged pools at the row's position (vector path only)
 };
@@ -97,6 +100,15 @@ struct LinearArgs {
   bf16_t* out_planes = nullptr;
   float* out_ssq = nullptr;
   const float* out_gain = nullptr;
+  // EPI_CROSS: n_tab device pointers, matrix 2l the keys' and 2l + 1 the values' projection of layer
+  // l, n_per rows each; destinations [layer][cross_batch][n_heads][n_visual][d_head] of kvdtype
+  const void* const* wtab = nullptr;
+  int n_tab = 0;
+  int tab_z = 1;  // set by the launcher
+  void* cross_k = nullptr;
+  void* cross_v = nullptr;
+  int cross_batch = 0;
+  int n_visual = 0;
   // Long row blocks, residual projections (y += W . x): partial products over ranges of K, float32
   // [kpart_max][kpart_rows][kpart_ld], which a second launch adds to y in range order; null keeps
   // one pass over K.  ksplit is set by the launcher.
@@ -216,19 +228,21 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
 // and values are fixed once prefilled):
 //   fq[h*nv + j][k] = sum_e K[h][j][e] * Wq[h*dh + e][k]   ([H*nv][d]: scores = fq . norm(x))
 //   fo[n][h*nv + j] = sum_e Wo[n][h*dh + e] * V[h][j][e]   ([d][H*nv]: out = fo . softmax(scores))
-// xk / xv: [H][nv][dh] of kvdtype; wq [H*dh][d], wo [d][H*dh] of wdtype.
+// for all n_layers layers in one launch each: layer l's keys and values at xk / xv + l * kv_stride
+// elements ([H][nv][dh] of kvdtype), its matrices wq[l] [H*dh][d] and wo[l] [d][H*dh] (device tables
+// of pointers, wdtype), fq and fo one after the other.
 bool cross_fold_ok(int nv, int dh);
-hipError_t launch_cross_fold(const void* xk, const void* xv, int kvdtype, const void* wq,
-                             const void* wo, int wdtype, int H, int nv, int dh, int d, float* fq,
-                             float* fo, hipStream_t s);
+hipError_t launch_cross_fold(const void* xk, const void* xv, size_t kv_stride, int kvdtype,
+                             const void* const* wq, const void* const* wo, int wdtype, int n_layers,
+                             int H, int nv, int dh, int d, float* fq, float* fo, hipStream_t s);
 
 // The scores of the folded cross-attention taken from the layer's input and attention output
 // instead of its post-attention residual (one-row steps): with F = fold_q diag(g) (g the
 // cross-attention RMSNorm gain) and W_o the self-attention output matrix, fg[j] = [F[j] | (F W_o)[j]]
 // ([HN][d + HD] float32), so fg . [x; o] = F (x + W_o o).  fold_q [HN][d] float32, wo [d][HD] in
-// wdtype.
-hipError_t launch_fold_fg(const float* fold_q, const float* gain, const void* wo, int wdtype,
-                          int HN, int d, int HD, float* fg, hipStream_t s);
+// wdtype; n_layers layers one after the other, gain and wo device tables of pointers.
+hipError_t launch_fold_fg(const float* fold_q, const float* const* gain, const void* const* wo,
+                          int wdtype, int n_layers, int HN, int d, int HD, float* fg, hipStream_t s);
 
 // Confidence-stopped drafting, evaluated by the final argmax of draft step `step` (row m =
 // sequence m): conf = the row's largest softmax probability, 1 / sum_n exp(logits[n] - max),

@@ -37,7 +37,7 @@ struct Layout {
       p_x, p_attn, p_ffn, p_inh, ssq, attn_part, fold_q, fold_o,
       bucket, rope_cos, rope_sin, status, cur_tok, g_pending, g_draft, g_target,
       g_count, g_active, g_nactive, g_stats, g_ndraft, g_drafting, g_draft_w, conf_lg,
-      fold_fg, kpart, total;
+      fold_fg, kpart, wtab, total;
   int rows_max, head_rows, parts_max, ctx_max, plane_rows, attn_rows;
   int kpart_max = 0;  // K-range partials of the long row blocks' residual projections
   bool fold = false;  // the folded cross-attention matrices are carved (fold_q, fold_o)
@@ -128,6 +128,9 @@ bool make_layout(const ssd_dims& d, Layout& L, bool allow_fold = true) {
   L.bucket = take(d.arch == SSD_ARCH_T5 ? (size_t)d.max_seq * 4 : 0);
   L.rope_cos = take(d.arch == SSD_ARCH_LLAMA ? (size_t)d.max_seq * (d.d_head / 2) * 4 : 0);
   L.rope_sin = take(d.arch == SSD_ARCH_LLAMA ? (size_t)d.max_seq * (d.d_head / 2) * 4 : 0);
+  // T5: device tables of the layers' pointers for launches over all layers: the cross-attention key
+  // and value matrices (interleaved), its query and output matrices, its norm gains, W_o
+  L.wtab = take(d.arch == SSD_ARCH_T5 ? (size_t)6 * d.n_layers * sizeof(void*) : 0);
   L.status = take(4);
   L.g_pending = take(B * 4);
   L.g_draft = take(B * (G > 0 ? G : 1) * 4);
@@ -230,6 +233,11 @@ struct ssd_ctx {
     return (size_t)d.max_batch * d.n_heads * d.n_visual * d.d_head;
   }
   size_t kv_elem() const { return d.kvdtype == SSD_BF16 ? 2 : 4; }
+  // device tables of pointers (Layout::wtab): 0 cross keys / values, 2 cross query, 3 cross output,
+  // 4 cross norm gain, 5 W_o (entry 0 holds two pointers a layer)
+  const void* const* table(int t) {
+    return reinterpret_cast<const void* const*>(ws + L.wtab) + (size_t)t * d.n_layers;
+  }
   size_t fold_layer_elems() const { return (size_t)d.n_heads * d.n_visual * d.d_model; }
   float* fg_layer(int l) {
     return reinterpret_cast<float*>(ws + L.fold_fg) +
@@ -795,6 +803,18 @@ int init_ctx(ssd_ctx* c, const ssd_dims& d, const ssd_weights* w, const ssd_kv* 
       return (int32_t)t5_bucket((int)n, d.rel_buckets, d.rel_max_dist);
     }, c->stream);
     if (rc) return rc;
+    const int nl = d.n_layers;
+    rc = upload_table(const_cast<const void**>(c->table(0)), (size_t)6 * nl, [&](size_t i) -> const void* {
+      if (i < (size_t)2 * nl) return i % 2 ? c->layers[i / 2].xv : c->layers[i / 2].xk;
+      const ssd_layer_weights& lw = c->layers[i % nl];
+      switch (i / nl) {
+        case 2: return lw.xq;
+        case 3: return lw.xo;
+        case 4: return lw.xattn_norm;
+        default: return lw.wo;
+      }
+    }, c->stream);
+    if (rc) return rc;
     HIP_TRY(launch_bias_table(w->rel_bias, c->at<int32_t>(L.bucket), d.n_heads, d.max_seq,
                               c->at<float>(L.bias_tab), c->stream));
   } else {
@@ -946,22 +966,26 @@ int ssd_prefill(ssd_ctx* c, int B, int P, const int32_t* d_prompt, const void* d
     const int MV = B * d.n_visual;
     const bool planes = MV >= 2 && d.wdtype == SSD_BF16;
     bf16_t* p_x = c->at<bf16_t>(c->L.p_x);
-    if (planes)
+    if (planes) {
+      // all layers' projections in one launch, stored to the caches
       HIP_TRY(launch_rows_prep(vis, D, MV, D, nullptr, nullptr, 0.f, p_x, nullptr, s));
-    for (int l = 0; l < d.n_layers; ++l) {
-      for (int which = 0; which < 2; ++which) {
-        LinearArgs a = lin(c);
-        a.x = vis; a.ldx = D; a.M = MV; a.K = D;
-        a.w[0] = which ? c->layers[l].xv : c->layers[l].xk; a.n_per = HD;
-        a.epi = EPI_STORE; a.y = tmp; a.ldy = HD;
-        if (planes) {
-          a.in_planes = p_x;
-          HIP_TRY(launch_linear_rows(a, s));
-        } else {
+      LinearArgs a = lin(c);
+      a.M = MV; a.K = D; a.n_per = HD; a.epi = EPI_CROSS; a.in_planes = p_x;
+      a.wtab = c->table(0); a.n_tab = 2 * d.n_layers;
+      a.cross_k = c->kv.xk; a.cross_v = c->kv.xv; a.cross_batch = d.max_batch;
+      a.n_visual = d.n_visual; a.n_heads = d.n_heads; a.d_head = d.d_head; a.kvdtype = d.kvdtype;
+      HIP_TRY(launch_linear_rows(a, s));
+    } else {
+      for (int l = 0; l < d.n_layers; ++l) {
+        for (int which = 0; which < 2; ++which) {
+          LinearArgs a = lin(c);
+          a.x = vis; a.ldx = D; a.M = MV; a.K = D;
+          a.w[0] = which ? c->layers[l].xv : c->layers[l].xk; a.n_per = HD;
+          a.epi = EPI_STORE; a.y = tmp; a.ldy = HD;
           HIP_TRY(run_linear(c, a));
+          void* dst = (char*)(which ? c->kv.xv : c->kv.xk) + (size_t)l * c->xkv_layer_elems() * c->kv_elem();
+          HIP_TRY(launch_scatter_cross(tmp, dst, B, d.n_visual, d.n_heads, d.d_head, d.kvdtype, s));
         }
-        void* dst = (char*)(which ? c->kv.xv : c->kv.xk) + (size_t)l * c->xkv_layer_elems() * c->kv_elem();
-        HIP_TRY(launch_scatter_cross(tmp, dst, B, d.n_visual, d.n_heads, d.d_head, d.kvdtype, s));
       }
     }
     // The folded cross-attention of every layer (and the folded-scores products of layers 1..k)
@@ -981,18 +1005,13 @@ int ssd_prefill(ssd_ctx* c, int B, int P, const int32_t* d_prompt, const void* d
       }
       HIP_TRY(hipEventRecord(c->ev_fork, s));
       HIP_TRY(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-      for (int l = 0; l < d.n_layers; ++l) {
-        const size_t off = (size_t)l * c->xkv_layer_elems() * c->kv_elem();
-        float* fq = c->at<float>(c->L.fold_q) + (size_t)l * c->fold_layer_elems();
-        HIP_TRY(launch_cross_fold((char*)c->kv.xk + off, (char*)c->kv.xv + off, d.kvdtype,
-                                  c->layers[l].xq, c->layers[l].xo, d.wdtype, d.n_heads,
-                                  d.n_visual, d.d_head, D, fq,
-                                  c->at<float>(c->L.fold_o) + (size_t)l * c->fold_layer_elems(),
-                                  c->side));
-        if (c->L.fg && l < d.draft_layers)
-          HIP_TRY(launch_fold_fg(fq, c->layers[l].xattn_norm, c->layers[l].wo, d.wdtype,
-                                 d.n_heads * d.n_visual, D, HD, c->fg_layer(l), c->side));
-      }
+      HIP_TRY(launch_cross_fold(c->kv.xk, c->kv.xv, c->xkv_layer_elems(), d.kvdtype, c->table(2),
+                                c->table(3), d.wdtype, d.n_layers, d.n_heads, d.n_visual, d.d_head, D,
+                                c->at<float>(c->L.fold_q), c->at<float>(c->L.fold_o), c->side));
+      if (c->L.fg)
+        HIP_TRY(launch_fold_fg(c->at<float>(c->L.fold_q),
+                               reinterpret_cast<const float* const*>(c->table(4)), c->table(5), d.wdtype,
+                               d.draft_layers, d.n_heads * d.n_visual, D, HD, c->fg_layer(0), c->side));
       HIP_TRY(hipEventRecord(c->ev_join, c->side));
       side_used = true;
     }
