@@ -147,12 +147,13 @@ __global__ __launch_bounds__(256) void ksum_rows_kernel(const LinearArgs a, int 
 }
 
 // QKV column tiles: tiles 2u and 2u + 1 of 16 features are columns c .. c + 15 and c + dh/2 ..
-// c + dh/2 + 15 of one head of one matrix (the rotary pairs); returns the matrix and c.
+// c + dh/2 + 15 of one head of one matrix (the rotary pairs; d_head is 64 or 128); returns the
+// matrix and c.
 __device__ __forceinline__ void qkv_pair_tile(const LinearArgs& a, int u, int& mat, int& c) {
-  const int per_head = a.d_head >> 5, per_mat = a.n_heads * per_head;
-  mat = u / per_mat;
-  const int rem = u - mat * per_mat, h = rem / per_head;
-  c = h * a.d_head + 16 * (rem - h * per_head);
+  const int sh = __builtin_ctz(a.d_head >> 5), per_mat = a.n_heads << sh;
+  mat = u >= 2 * per_mat ? 2 : (u >= per_mat ? 1 : 0);
+  const int rem = u - mat * per_mat, h = rem >> sh;
+  c = h * a.d_head + 16 * (rem - (h << sh));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -270,7 +271,13 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
     constexpr int TP = 256 / BM;  // threads per row
     const int row = tid / TP, p0 = tid % TP, m = min(m0 + row, M - 1);
     float s2 = 0.f;
-    for (int p = p0; p < a.in_nssq; p += TP) s2 += a.in_ssq[(size_t)p * ssq_ld + m];
+    for (int p = p0; p < a.in_nssq; p += 16 * TP) {  // 16 requested together (up to 128 partials a row)
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = a.in_ssq[(size_t)min(p + u * TP, a.in_nssq - 1) * ssq_ld + m];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s2 += p + u * TP < a.in_nssq ? v[u] : 0.f;
+    }
 #pragma unroll
     for (int o = 1; o < TP; o <<= 1) s2 += __shfl_xor(s2, o, SSD_WAVE);
     if (p0 == 0) rs[row] = 1.0f / sqrtf(s2 / (float)K + a.eps);
@@ -285,32 +292,60 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
   const unsigned char* fa = ring + (size_t)(wm * 2 * MI) * 1024 + lane * 16;
   const unsigned char* fw = ring + AP * 1024 + (size_t)(wn * 16 * NJ + c) * (RK * 2);
   const int wpos[2] = {KB == 1 ? (g ^ ((c >> 1) & 3)) << 4 : (g ^ (c & 7)) << 4, ((4 + g) ^ (c & 7)) << 4};
-  for (int kt = 0; kt < nk; ++kt) {
-    // step kt has landed (this wave's own loads; with the barrier everyone's), and everyone is done
-    // with the stage the next fetch overwrites
-    // (up to NS - 2 later steps, as many as there are, stay in flight)
+  // step kt has landed (this wave's own loads; with the barrier everyone's), and everyone is done with
+  // the stage the next fetch overwrites (up to NS - 2 later steps, as many as there are, stay in flight)
+  auto land = [&](int kt) {
     if (NS >= 4 && kt + 2 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(2 * PW) : "memory");
     else if (NS >= 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(PW) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (kt + NS - 1 < nk) fetch(kt + NS - 1);
+  };
+  struct Frags {
+    bf16x8_t h[MI], l[MI], w[NJ];
+  };
+  auto read = [&](Frags& f, int kt, int kb2) {
     const size_t st = (size_t)(kt % NS) * STAGE;
 #pragma unroll
-    for (int kb2 = 0; kb2 < KB; ++kb2) {
-      bf16x8_t h[MI], l[MI], w[NJ];
+    for (int j = 0; j < NJ; ++j) f.w[j] = *reinterpret_cast<const bf16x8_t*>(fw + st + j * (16 * RK * 2) + wpos[kb2]);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) w[j] = *reinterpret_cast<const bf16x8_t*>(fw + st + j * (16 * RK * 2) + wpos[kb2]);
+    for (int i = 0; i < MI; ++i) f.h[i] = *reinterpret_cast<const bf16x8_t*>(fa + st + kb2 * (RGS * 2048) + i * 2048);
 #pragma unroll
-      for (int i = 0; i < MI; ++i) h[i] = *reinterpret_cast<const bf16x8_t*>(fa + st + kb2 * (RGS * 2048) + i * 2048);
+    for (int i = 0; i < MI; ++i) f.l[i] = *reinterpret_cast<const bf16x8_t*>(fa + st + kb2 * (RGS * 2048) + i * 2048 + 1024);
+  };
+  auto mul = [&](const Frags& f) {
 #pragma unroll
-      for (int i = 0; i < MI; ++i) l[i] = *reinterpret_cast<const bf16x8_t*>(fa + st + kb2 * (RGS * 2048) + i * 2048 + 1024);
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
+      for (int i = 0; i < MI; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[j], f.h[i], acc[j][i], 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < MI; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], h[i], acc[j][i], 0, 0, 0);
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int i = 0; i < MI; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], l[i], acc[j][i], 0, 0, 0);
+      for (int i = 0; i < MI; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[j], f.l[i], acc[j][i], 0, 0, 0);
+  };
+  if constexpr (KB == 2) {
+    // a K block's operands are read ahead of the products of the one before
+    Frags f0, f1;
+    land(0);
+    read(f0, 0, 0);
+    for (int kt = 0; kt < nk; ++kt) {
+      read(f1, kt, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (kt + 1 < nk) {
+        land(kt + 1);
+        read(f0, kt + 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mul(f1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    for (int kt = 0; kt < nk; ++kt) {
+      Frags f;
+      land(kt);
+      read(f, kt, 0);
+      mul(f);
     }
   }
   if (rms) __syncthreads();
@@ -335,7 +370,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
         if (!rok || tile * 16 >= n_out) continue;
         int mat, c0;
         qkv_pair_tile(a, tile >> 1, mat, c0);
-        const int hh = c0 / a.d_head, d = c0 - hh * a.d_head + 4 * g;
+        const int hh = c0 >> __builtin_ctz(a.d_head), d = (c0 & (a.d_head - 1)) + 4 * g;
         float v0[4], v1[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v0[e] = acc[2 * u][i][e] * rsc; v1[e] = acc[2 * u + 1][i][e] * rsc; }
@@ -498,46 +533,56 @@ RowsShape rows_shape(int n_out, int M, int epi) {
   return best;
 }
 
-// Launch shape of gemm_ring_kernel: tile rows 32 MI, features 32 NJ, K ranges.
-struct RingShape {
-  int mi, nj, ksplit;
+// Forms of gemm_ring_kernel and their measured time (us) per 32-element K step of a compute unit that
+// holds 1, 2, ... of their blocks at once (as many as fit its LDS): a lone block's waves wait for
+// each other at every step, so small grids want small tiles, and the large tile pays only where two
+// of its blocks share a unit.  (Measured over 160..1216 rows, 2048..12288 features, K 2048..11008;
+// against 128 x 128 tiles alone: QKV of 488 rows at the FlanT5-xl shape 45 -> 28 us, W_o 25 -> 17,
+// gate/up 77 -> 57.)
+struct RingForm {
+  int mi, nj, kb, ns, fit;
+  double us[4];
+};
+constexpr RingForm RING_FORMS[6] = {
+    {4, 8, 1, 2, 2, {1.0, 1.42, 0, 0}},      // 128 x 256
+    {4, 4, 1, 2, 3, {0.61, 0.85, 1.27, 0}},  // 128 x 128
+    {2, 4, 1, 2, 4, {0.49, 0.58, 0.87, 1.1}},  // 64 x 128, two stages
+    {2, 4, 1, 4, 2, {0.36, 0.52, 0, 0}},     // 64 x 128, four stages
+    {2, 2, 2, 2, 3, {0.31, 0.40, 0.50, 0}},  // 64 x 64, steps of 64
+    {2, 2, 1, 4, 3, {0.25, 0.38, 0.51, 0}},  // 64 x 64, four stages
 };
 
-RingShape ring_shape(int n_out, int M, int K, bool gated, bool can_split, int kpart_max) {
-  const long long cus = cu_count();
-  const int width = gated ? 2 * n_out : n_out;
-  auto blocks = [&](int mi, int nj) {
-    return (long long)((M + 32 * mi - 1) / (32 * mi)) * ((width + 32 * nj - 1) / (32 * nj));
-  };
-  // time of a form: rounds of blocks x the products of a block / the rate the form reaches
-  const int forms[3][2] = {{4, 8}, {4, 4}, {2, 4}};
-  const double rate[3] = {1.0, 0.8, 0.65};
-  RingShape best = {4, 8, 1};
+struct RingShape {
+  int form, ksplit;
+};
+
+// The form, and for residual projections the number of K ranges, with the least estimated time.
+RingShape ring_shape(int width, int M, int K, bool can_split, int kpart_max) {
+  const int cus = cu_count(), steps = K / 32;
+  RingShape best = {0, 1};
   double best_t = -1.0;
-  for (int f = 0; f < 3; ++f) {
-    const int mi = forms[f][0], nj = forms[f][1];
-    const long long b = blocks(mi, nj);
-    int smax = 1;
-    if (can_split && b < 2 * cus) {
-      smax = (int)(2 * cus / b);
-      if (smax > kpart_max) smax = kpart_max;
-      if (smax > 4) smax = 4;
-      if (smax < 1) smax = 1;
-      const int nk = K / 64;  // the smaller forms' steps (the large one has twice as many)
-      while (smax > 1 && (nk + smax - 1) / smax * (smax - 1) >= nk) --smax;  // every range holds a step
-    }
-    const long long n = b * smax, rounds = (n + cus - 1) / cus;
-    const double t = (double)rounds * mi * nj / (smax * rate[f]);
-    if (best_t < 0.0 || t < best_t) {
-      best = {mi, nj, smax};
-      best_t = t;
+  for (int f = 0; f < 6; ++f) {
+    const RingForm& rf = RING_FORMS[f];
+    const long long tiles = (long long)((M + 32 * rf.mi - 1) / (32 * rf.mi)) * ((width + 32 * rf.nj - 1) / (32 * rf.nj));
+    for (int S = 1; S <= (can_split ? (kpart_max < 4 ? kpart_max : 4) : 1); ++S) {
+      const int nk = steps / rf.kb, per = (nk + S - 1) / S;
+      if ((long long)per * (S - 1) >= nk) break;  // every range holds a step
+      const long long r = (tiles * S + cus - 1) / cus, full = r / rf.fit, rest = r % rf.fit;
+      double t = (double)(per * rf.kb) * (full * rf.us[rf.fit - 1] + (rest ? rf.us[rest - 1] : 0.0));
+      // the second launch: its latency, the partials and the residual
+      if (S > 1) t += 3.0 + (double)M * width * (S + 4) * 4.0 / 6.0e6;
+      if (best_t < 0.0 || t < best_t) {
+        best = {f, S};
+        best_t = t;
+      }
     }
   }
   return best;
 }
 
-template <int KIND, int MI, int NJ, int KB, int NS>
+template <int KIND, int F>
 hipError_t launch_ring_t(const LinearArgs& a, int n_out, hipStream_t s) {
+  constexpr int MI = RING_FORMS[F].mi, NJ = RING_FORMS[F].nj, KB = RING_FORMS[F].kb, NS = RING_FORMS[F].ns;
   constexpr int shm = ring_lds<MI, NJ, KB, NS>();
   if constexpr (shm > 60 * 1024) {
     static bool attr = false;
@@ -554,10 +599,15 @@ hipError_t launch_ring_t(const LinearArgs& a, int n_out, hipStream_t s) {
 }
 
 template <int KIND>
-hipError_t launch_ring(const LinearArgs& a, RingShape sh, int n_out, hipStream_t s) {
-  if (sh.nj == 8) return launch_ring_t<KIND, 4, 8, 1, 2>(a, n_out, s);
-  if (sh.mi == 4) return launch_ring_t<KIND, 4, 4, 2, 3>(a, n_out, s);
-  return launch_ring_t<KIND, 2, 4, 2, 4>(a, n_out, s);
+hipError_t launch_ring(const LinearArgs& a, int form, int n_out, hipStream_t s) {
+  switch (form) {
+    case 0: return launch_ring_t<KIND, 0>(a, n_out, s);
+    case 1: return launch_ring_t<KIND, 1>(a, n_out, s);
+    case 2: return launch_ring_t<KIND, 2>(a, n_out, s);
+    case 3: return launch_ring_t<KIND, 3>(a, n_out, s);
+    case 4: return launch_ring_t<KIND, 4>(a, n_out, s);
+    default: return launch_ring_t<KIND, 5>(a, n_out, s);
+  }
 }
 
 constexpr int ROWS_MAX = 128;  // rows the weight-streaming form takes
@@ -576,7 +626,7 @@ hipError_t launch_rows_prep(const float* x, int ldx, int M, int K, const float* 
 size_t rows_ssq_floats(int d_model, int rows) {
   const size_t tiles = (size_t)(d_model + 15) / 16;
   const size_t few = tiles * 2 * 16, mid = tiles * (size_t)((rows < ROWS_MAX ? rows : ROWS_MAX) + 15),
-               big = (size_t)(d_model / 64 + 2) * (size_t)(rows + 15);
+               big = (size_t)(d_model / 32 + 2) * (size_t)(rows + 15);
   const size_t m = few > mid ? few : mid;
   return m > big ? m : big;
 }
@@ -619,17 +669,18 @@ hipError_t launch_linear_rows(const LinearArgs& args, hipStream_t s, int* n_part
   const bool vec = b.epi == EPI_ARGMAX || (n_out % 8 == 0 && b.n_per % 4 == 0);
   if (!vec) return hipErrorInvalidValue;
   const bool split = b.epi == EPI_RESID && b.kpart && n_out <= b.kpart_ld;
-  const RingShape sh = ring_shape(cross ? n_out * a.n_tab : n_out, a.M, a.K, gated, split, a.kpart_max);
+  const int width = gated ? 2 * n_out : n_out;
+  const RingShape sh = ring_shape(cross ? n_out * a.n_tab : width, a.M, a.K, split, a.kpart_max);
   b.ksplit = sh.ksplit;
-  const int cols = ((gated ? 2 * n_out : n_out) + 32 * sh.nj - 1) / (32 * sh.nj);
+  const int nj = RING_FORMS[sh.form].nj, cols = (width + 32 * nj - 1) / (32 * nj);
   if (b.epi == EPI_ARGMAX) b.n_parts = 2 * cols;
   if (n_parts) *n_parts = b.n_parts;
   const int slices = (n_out + KSUM_COLS - 1) / KSUM_COLS;
   if (n_ssq) *n_ssq = sh.ksplit > 1 ? slices : 2 * cols;
-  hipError_t e = gated ? launch_ring<RING_GATED>(b, sh, n_out, s)
-                       : (cross ? launch_ring<RING_CROSS>(b, sh, n_out, s)
-                       : b.epi == EPI_QKV ? launch_ring<RING_QKV>(b, sh, n_out, s)
-                                           : launch_ring<RING_PLAIN>(b, sh, n_out, s));
+  hipError_t e = gated ? launch_ring<RING_GATED>(b, sh.form, n_out, s)
+                       : (cross ? launch_ring<RING_CROSS>(b, sh.form, n_out, s)
+                       : b.epi == EPI_QKV ? launch_ring<RING_QKV>(b, sh.form, n_out, s)
+                                           : launch_ring<RING_PLAIN>(b, sh.form, n_out, s));
   if (e != hipSuccess || sh.ksplit == 1) return e;
   hipLaunchKernelGGL(ksum_rows_kernel, dim3(a.row_groups, slices), dim3(256), 0, s, b, n_out);
   return hipGetLastError();
