@@ -183,34 +183,44 @@ __global__ __launch_bounds__(256) void gemv_kernel(const LinearArgs a) {
   gemv_finish<WT, MB, GV_ANY>(a, r, acc, yold, live, m0, mrows, tid, lane, wave, rv, ri);
 }
 
-constexpr int SKW = 4;  // waves of a block of the folded cross-attention kernel
+constexpr int SKW = 8;  // waves of a block of the folded cross-attention kernel
 constexpr int SSQ_MAX = 256;  // partial sums of squares it reads
 
 // The folded cross-attention of a verify chunk (at most 8 rows, float32 weights) on half tiles.  A
 // half tile is 8 features: the A operand holds them twice, A row i being feature i & 7 over elements
 // 0..31 (i < 8) or 32..63 (i >= 8) of a 64-element step, and the B operand's columns are the 8 input
 // rows over the same two halves; D[f][t] + D[f + 8][t + 8] is the step's dot product (the other two
-// quadrants are cross terms and are dropped).  A lane reads its 8 weights as 32 bytes and splits
-// them into bf16 hi / lo; a step takes the products hi.hi, hi.lo and lo.hi (about 16 mantissa bits
-// on both sides).  Four waves split K; the epilogue runs on 64 threads (feature tid / 8, row tid % 8).
+// quadrants are cross terms and are dropped).  A step's weights are read as 256 contiguous bytes of a
+// row, eight lanes each, split into bf16 hi / lo and passed through the wave's own LDS to the operand
+// order (a row per lane is 64 accesses of the vector memory path a load instead of 16).  With eight
+// waves to split K instead of four: 6.2 -> 6.0 us for the scores and 7.2 -> 6.5 for the output of 6 rows
+// at the FlanT5-xl shape, 4.4 -> 3.6 and 4.8 -> 4.2 at FlanT5-base; what is left is the launch, one round
+// trip of loads and the reduction.  A step takes the products hi.hi, hi.lo and lo.hi (about 16 mantissa
+// bits on both sides).  The epilogue runs on 64 threads (feature tid / 8, row tid % 8).
 // RMS: the scores, fold_q . rms(x) from input planes, stored.  Else the output, y += fold_o .
 // softmax(scores): the input is float32 rows (in_f32) turned into softmax probabilities over groups of
 // a.group consecutive inputs (8, 16 or 32: the group of a lane's 8 elements spans the 1, 2 or 4 lanes
 // l, l ^ 16, l ^ 32, l ^ 48 of one row and step half), split into hi / lo as the B operand; it leaves
 // the next planes and one partial sum of squares per half tile.
 template <bool RMS, int SK>
-__global__ __launch_bounds__(64 * SKW, 2) void fold_rows_kernel(const LinearArgs a) {
+__global__ __launch_bounds__(64 * SKW) void fold_rows_kernel(const LinearArgs a) {
   constexpr bool SMX = !RMS;
   constexpr int NG = 4 * SKW;  // groups of 16 threads
   __shared__ float part[SKW][8][9];
   __shared__ float rs[16];
   __shared__ float ssq_red[4 * SKW][16];
+  __shared__ __attribute__((aligned(16))) unsigned char staged[SKW][2][1024];  // hi, lo: [8 rows][64]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int K = a.K, M = a.M, n_out = a.n_per, h = blockIdx.x;
   const int steps = K / 64;
   const int s_beg = (steps * wave) / SKW, s_end = (steps * (wave + 1)) / SKW;
-  const float* wrow = reinterpret_cast<const float*>(a.w[0]) + (size_t)min(h * 8 + (lane & 7), n_out - 1) * K;
+  // this lane's weights of a step: row lane / 8, elements 4 (lane % 8) .. and 32 + 4 (lane % 8) ..
+  const float* wrow = reinterpret_cast<const float*>(a.w[0]) + (size_t)min(h * 8 + (lane >> 3), n_out - 1) * K + (lane & 7) * 4;
+  // staging: 16-byte chunk k of row r at position k ^ r
+  unsigned char* st_w = staged[wave][0] + (lane >> 3) * 128 + (lane & 1) * 8;
+  const int wp0 = (((lane & 7) >> 1) ^ (lane >> 3)) << 4, wp1 = ((4 + ((lane & 7) >> 1)) ^ (lane >> 3)) << 4;
+  const unsigned char* st_r = staged[wave][0] + (lane & 7) * 128 + (((4 * ((lane >> 3) & 1) + (lane >> 4)) ^ (lane & 7)) << 4);
   const int kq = ((lane >> 3) & 1) * 32 + (lane >> 4) * 8;  // this lane's 8 elements of a step
   const int tok = lane & 7;
   const bool tok_ok = tok < M;
@@ -235,11 +245,11 @@ __global__ __launch_bounds__(64 * SKW, 2) void fold_rows_kernel(const LinearArgs
   f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int s0 = s_beg; s0 < s_end; s0 += SK) {
     uint4 bv[SK][2];   // the hi and lo planes' 16 bytes, or 32 bytes of the float32 row
-    float4 wf[SK][2];
+    f32x4_t wf[SK][2];
     // inputs first (L2-resident, they arrive early), then the weights in step order
 #pragma unroll
     for (int u = 0; u < SK; ++u) {
-      const int st = min(s0 + u, s_end - 1);
+      const int st = max(min(s0 + u, s_end - 1), 0);
       if (SMX) {
         const float4 f0 = *reinterpret_cast<const float4*>(frow + st * 64 + kq);
         const float4 f1 = *reinterpret_cast<const float4*>(frow + st * 64 + kq + 4);
@@ -253,9 +263,9 @@ __global__ __launch_bounds__(64 * SKW, 2) void fold_rows_kernel(const LinearArgs
     }
 #pragma unroll
     for (int u = 0; u < SK; ++u) {
-      const int k0 = min(s0 + u, s_end - 1) * 64 + kq;
-      wf[u][0] = *reinterpret_cast<const float4*>(wrow + k0);
-      wf[u][1] = *reinterpret_cast<const float4*>(wrow + k0 + 4);
+      const int k0 = max(min(s0 + u, s_end - 1), 0) * 64;
+      wf[u][0] = *reinterpret_cast<const f32x4_t*>(wrow + k0);
+      wf[u][1] = *reinterpret_cast<const f32x4_t*>(wrow + k0 + 32);
     }
     __builtin_amdgcn_sched_barrier(0);  // keep the whole batch in flight before the first MFMA
 #pragma unroll
@@ -291,9 +301,17 @@ __global__ __launch_bounds__(64 * SKW, 2) void fold_rows_kernel(const LinearArgs
       // operands as values (no address taken, so that nothing of the batch lives in memory)
       const bf16x8_t B0 = __builtin_bit_cast(bf16x8_t, use ? b0 : z);
       const bf16x8_t B1 = __builtin_bit_cast(bf16x8_t, use ? b1 : z);
-      uint4 whi, wlo;
-      split_bf16x8_v(wf[u][0], wf[u][1], whi, wlo);
-      const bf16x8_t Ah = __builtin_bit_cast(bf16x8_t, whi), Al = __builtin_bit_cast(bf16x8_t, wlo);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f32x4_t f = wf[u][q];
+        const uint32_t h0 = pack_bf16x2(f[0], f[1]), h1 = pack_bf16x2(f[2], f[3]);
+        unsigned char* p = st_w + (q ? wp1 : wp0);
+        *reinterpret_cast<uint2*>(p) = make_uint2(h0, h1);
+        *reinterpret_cast<uint2*>(p + 1024) =
+            make_uint2(pack_bf16x2(f[0] - __uint_as_float(h0 << 16), f[1] - __uint_as_float(h0 & 0xffff0000u)),
+                       pack_bf16x2(f[2] - __uint_as_float(h1 << 16), f[3] - __uint_as_float(h1 & 0xffff0000u)));
+      }
+      const bf16x8_t Ah = *reinterpret_cast<const bf16x8_t*>(st_r), Al = *reinterpret_cast<const bf16x8_t*>(st_r + 1024);
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, B0, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, B1, acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Al, B0, acc, 0, 0, 0);
