@@ -580,3 +580,42 @@ def test_verify_chunk_at_the_skinny_capacity(wl):
     assert toks.cpu().numpy().tolist() == run.tokens
     assert stats["rounds"] == len(run.rounds)
     assert dd.sync_status() == (0, 0)
+
+
+@pytest.mark.parametrize("arch,batch,gamma,kv,extra", [
+    ("t5", 1, 1, "f32", 0), ("t5", 1, 7, "bf16", 0), ("llama", 1, 8, "f32", 0),
+    ("llama", 1, 15, "bf16", 260), ("t5", 1, 16, "f32", 0), ("llama", 2, 15, "f32", 260),
+    ("t5", 3, 10, "bf16", 0), ("t5", 4, 11, "f32", 0), ("llama", 7, 6, "bf16", 260),
+    ("llama", 8, 7, "f32", 0), ("t5", 9, 6, "f32", 260), ("t5", 13, 4, "bf16", 0),
+    ("llama", 43, 2, "f32", 0)],
+    ids=lambda v: str(v))
+def test_row_counts_at_the_edges_of_the_plane_kernels(arch, batch, gamma, kv, extra, monkeypatch):
+    """Verify chunks of 2, 8, 9, 16, 17, 32, 33, 44, 49, 63, 64, 65 and 129 rows: the edges of the
+    16-row groups, of the row groups a block of the few-row kernel takes and of the step from it to
+    the many-row kernel (129), and draft steps of 1, 2, 3, 4, 7, 8, 9, 13 and 43 rows (the imitation
+    network on planes past 8).  Widths of 5 or 6 64-element steps with an FFN of 13 or 15 leave K
+    splits and column tiles with remainders, the vocabulary is odd, and a page holds 5 positions.
+    The cache is float32 or bfloat16, over or under the 256 positions where keys are split."""
+    from dataclasses import replace
+    from functools import partial
+    from paper_2510_22641_amd import runtime
+    monkeypatch.setattr(runtime, "Capacity", partial(runtime.Capacity, page_size=5))
+    if arch == "t5":
+        sh = replace(synth.SMALL_T5_BF16, name="t5-edges", n_layers=3, d_model=320, n_heads=5, d_head=64,
+                     d_ff=832, vocab=1999, n_visual=8)
+        wl = synth.S_T5
+    else:
+        sh = replace(synth.SMALL_LLAMA_BF16, name="llama-edges", n_layers=3, d_model=384, n_heads=3,
+                     d_head=128, d_ff=960, vocab=1999, n_visual=9)
+        wl = synth.S_LLAMA
+    wl = wl.with_(name=sh.name, shape=sh, draft_layers=2, gamma=gamma, new_tokens=2 * gamma + 4)
+    w, z, pr = parity.workload_inputs(wl, 31, batch)
+    dd = runtime.from_workload(wl, 31, weights=w, max_batch=batch, page_seed=4, kv_dtype=kv,
+                               extra_seq=gamma + extra)
+    assert dd.cap.page_size == 5 and (dd.cap.max_seq >= 256) == (extra > 0)
+    dec = Decoder(wl.shape, w, wl.draft_layers)
+    pt, vt = dd.upload_inputs(pr, z)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, gamma, reuse=batch % 2 == 0, max_rounds=2)
+    assert dd.sync_status() == (0, 0)
+    for s in sorted({0, batch // 2, batch - 1}):
+        parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, gamma, max_rounds=2)
