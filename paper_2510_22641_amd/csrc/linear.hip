@@ -364,6 +364,128 @@ __global__ __launch_bounds__(64 * SKW) void fold_rows_kernel(const LinearArgs a)
   }
 }
 
+// The imitation network's two layers on 2..8 rows: bf16 weights against float32 rows (LN: normalised
+// first) on the float32 matrix instruction, so that inputs and accumulation stay float32.  Half tiles
+// of 8 features as in fold_rows_kernel: A rows 0..7 and 8..15 are the features over the two halves of a
+// 64-element step, the B columns the rows over the same halves, so a row's eight lanes read its whole
+// 128 bytes.  Matrix element e of a lane's group of 8 takes the group's elements in any order as long
+// as A and B agree, so both are read as contiguous 16-byte loads and no operand is rearranged.  Eight
+// waves split K, all loads of a block in flight at once; the rows' LayerNorm statistics come from the
+// same registers.  Bound by launch and one round trip.  The vector kernel stages the rows in LDS in
+// every block and multiplies each weight row by row: 26.6 -> 7.8 us (LN) and 13.5 -> 5.4 us for 8
+// rows of 2048 x 2048.
+template <bool LN, int SK>
+__global__ __launch_bounds__(64 * SKW) void dense_rows_kernel(const LinearArgs a) {
+  __shared__ float part[SKW][8][9];
+  __shared__ float st[SKW][2][8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = a.K, M = a.M, n_out = a.n_per, h = blockIdx.x;
+  const int steps = K / 64;
+  const int s_beg = (steps * wave) / SKW, s_end = (steps * (wave + 1)) / SKW;  // at most SK steps
+  const int kq = ((lane >> 3) & 1) * 32 + (lane >> 4) * 8;  // this lane's 8 elements of a step
+  const float* xrow = a.x + (size_t)min(lane & 7, M - 1) * a.ldx + kq;
+  const bf16_t* wrow = reinterpret_cast<const bf16_t*>(a.w[0]) + (size_t)min(h * 8 + (lane & 7), n_out - 1) * K + kq;
+  const int ef = (tid & 63) >> 3, et = tid & 7, en = h * 8 + ef, ec = min(en, n_out - 1), em = min(et, M - 1);
+
+  f32x4_t xv[SK][2], gv[LN ? SK : 1][2], bv[LN ? SK : 1][2];
+  uint4 wv[SK];
+#pragma unroll
+  for (int u = 0; u < SK; ++u) {
+    const float* p = xrow + max(min(s_beg + u, s_end - 1), 0) * 64;
+    xv[u][0] = *reinterpret_cast<const f32x4_t*>(p);
+    xv[u][1] = *reinterpret_cast<const f32x4_t*>(p + 4);
+  }
+#pragma unroll
+  for (int u = 0; u < SK; ++u)
+    wv[u] = *reinterpret_cast<const uint4*>(wrow + max(min(s_beg + u, s_end - 1), 0) * 64);
+  if constexpr (LN) {
+#pragma unroll
+    for (int u = 0; u < SK; ++u) {
+      const int k0 = max(min(s_beg + u, s_end - 1), 0) * 64 + kq;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        gv[u][q] = *reinterpret_cast<const f32x4_t*>(a.gain + k0 + 4 * q);
+        bv[u][q] = *reinterpret_cast<const f32x4_t*>(a.shift + k0 + 4 * q);
+      }
+    }
+  }
+  const float bias = a.bias ? a.bias[ec] : 0.f;
+  const float y_old = !LN && a.resid ? a.resid[(size_t)em * a.ldr + ec] : 0.f;
+  __builtin_amdgcn_sched_barrier(0);
+
+  if constexpr (LN) {
+    float p1 = 0.f, p2 = 0.f;
+#pragma unroll
+    for (int u = 0; u < SK; ++u) {
+      if (s_beg + u >= s_end) break;  // the same for the whole wave
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float v = xv[u][e >> 2][e & 3];
+        p1 += v;
+        p2 += v * v;
+      }
+    }
+#pragma unroll
+    for (int o = 8; o < SSD_WAVE; o <<= 1) {
+      p1 += __shfl_xor(p1, o, SSD_WAVE);
+      p2 += __shfl_xor(p2, o, SSD_WAVE);
+    }
+    if (lane < 8) { st[wave][0][lane] = p1; st[wave][1][lane] = p2; }
+    __syncthreads();
+    p1 = p2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < SKW; ++w) { p1 += st[w][0][lane & 7]; p2 += st[w][1][lane & 7]; }
+    const float mean = p1 / (float)K;
+    const float rstd = 1.0f / sqrtf(fmaxf(p2 / (float)K - mean * mean, 0.f) + a.eps);
+#pragma unroll
+    for (int u = 0; u < SK; ++u)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xv[u][q][e] = (xv[u][q][e] - mean) * rstd * gv[u][q][e] + bv[u][q][e];
+  }
+  f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < SK; ++u) {
+    if (s_beg + u >= s_end) break;
+    const uint32_t w4[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float wf = __uint_as_float(e & 1 ? w4[e >> 1] & 0xffff0000u : w4[e >> 1] << 16);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wf, xv[u][e >> 2][e & 3], acc, 0, 0, 0);
+    }
+  }
+  // the useful quadrants, as in fold_rows_kernel
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float v = acc[e] + __shfl_down(acc[e], 40, SSD_WAVE);
+    if (lane < 24 && !(lane & 8)) part[wave][4 * (lane >> 4) + e][lane & 7] = v;
+  }
+  __syncthreads();
+  if (tid >= 64 || et >= M || en >= n_out) return;
+  float v = 0.f;
+#pragma unroll
+  for (int w = 0; w < SKW; ++w) v += part[w][ef][et];
+  a.y[(size_t)et * a.ldy + en] = LN ? gelu_tanh(v + bias) : y_old + (v + bias);
+}
+
+// The rows of K a block's eight waves hold in registers: at most 8 steps of 64 each
+bool dense_rows_ok(const LinearArgs& a) {
+  return a.wdtype == 1 && a.M >= 2 && a.M <= 8 && a.n_mats == 1 && a.K % 64 == 0 && a.K <= 64 * SKW * 8 &&
+         a.ldx % 4 == 0 && a.bias &&
+         ((a.norm == NORM_LN && a.epi == EPI_BIAS_GELU) || (a.norm == NORM_NONE && a.epi == EPI_BIAS_RESID));
+}
+
+template <bool LN>
+hipError_t launch_dense_rows(const LinearArgs& a, hipStream_t s) {
+  const dim3 grid((a.n_per + 7) / 8), block(64 * SKW);
+  const int spw = (a.K / 64 + SKW - 1) / SKW;
+  if (spw <= 2) hipLaunchKernelGGL((dense_rows_kernel<LN, 2>), grid, block, 0, s, a);
+  else if (spw <= 4) hipLaunchKernelGGL((dense_rows_kernel<LN, 4>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((dense_rows_kernel<LN, 8>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 // Vector-path launch shape: MB input rows per block (grid.y = row blocks), blocks over row groups.
 struct GvPlan {
   int mb, blocks;
@@ -518,6 +640,7 @@ hipError_t launch_linear(LinearArgs a, hipStream_t s, int* n_parts, LaunchTiming
   bool one = false;
   const hipError_t e = launch_one_row(a, s, timing, &one);
   if (one) return e;
+  if (dense_rows_ok(a)) return a.norm == NORM_LN ? launch_dense_rows<true>(a, s) : launch_dense_rows<false>(a, s);
   return a.wdtype == 1 ? launch_gemv_t<bf16_t>(a, s, timing) : launch_gemv_t<float>(a, s, timing);
 }
 

@@ -619,3 +619,21 @@ def test_row_counts_at_the_edges_of_the_plane_kernels(arch, batch, gamma, kv, ex
     assert dd.sync_status() == (0, 0)
     for s in sorted({0, batch // 2, batch - 1}):
         parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, gamma, max_rounds=2)
+
+
+@pytest.mark.parametrize("batch,d_model,in_hidden", [(2, 320, 2112), (3, 2112, 64), (8, 1088, 1024),
+                                                     (5, 448, 4096), (8, 320, 4160)], ids=lambda v: str(v))
+def test_imitation_network_on_few_rows(batch, d_model, in_hidden):
+    """Draft steps of 2, 3, 5 and 8 rows: the imitation network's layers over 1 to 64 steps of 64
+    inputs, shared by eight waves (some without a step, some with one more than others), at each
+    register depth of the few-row kernel, at its largest width (4096) and one step past it (4160, the
+    vector kernel).  Every draft logit follows the oracle."""
+    from dataclasses import replace
+    sh = replace(synth.SMALL_T5_BF16, name="t5-imitation-rows", n_layers=2, d_model=d_model,
+                 n_heads=d_model // 64, d_head=64, d_ff=320, vocab=500, in_hidden=in_hidden)
+    wl = synth.S_T5.with_(name=sh.name, shape=sh, draft_layers=1, gamma=2, new_tokens=8)
+    dd, dec, pr, z, pt, vt = _setup(wl, seed=37, batch=batch, extra_seq=wl.gamma)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, reuse=True, max_rounds=2)
+    assert dd.sync_status() == (0, 0)
+    for s in sorted({0, batch - 1}):
+        parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=2)
