@@ -119,8 +119,9 @@ def prefill_timing(dd, pt, vt, reps: int = 3) -> float:
 
 
 def dominant_kernel_name(sh) -> str:
-    """rocprof name of the one-row GEMV instantiation that streams the RMS-normalised d_model-wide
-    matrices (the kernel the library times while profiling)."""
+    """rocprof name of the one-row GEMV that streams the RMS-normalised d_model-wide matrices (the
+    kernel the library times while profiling), without its last template argument: the epilogue,
+    which differs between the QKV, gate/up and LM-head launches."""
     d = sh.d_model
     if sh.dtype == "bf16" and 2048 <= d <= 6144 and d % 8 == 0:
         return "gemv1k_kernel<unsigned short, %d, 1>" % ((d + 2047) // 2048)
@@ -130,7 +131,7 @@ def dominant_kernel_name(sh) -> str:
 
 
 # the sources that define the one-row GEMV kernels (their hash ties a counter summary to them)
-GEMV_SOURCES = ("device.h", "gemv_common.h", "kernels.h", "linear.hip")
+GEMV_SOURCES = ("device.h", "gemv_common.h", "kernels.h", "gemv1.hip")
 
 
 def kernel_sources_sha256() -> str:
