@@ -203,7 +203,7 @@ __global__ __launch_bounds__(64 * NW) void attn_row_kernel(const AttnArgs a, con
     }
     return;
   }
-  y = l > 0.f ? y / l : 0.f;
+  y = l == 0.f ? 0.f : y / l;  // no key: zeros (a NaN score stays NaN)
   if (a.out) a.out[(size_t)r * HD + h * DH + tid] = y;
   if (a.out_planes) store_planes1(a.out_planes + plane_at(r, h * DH + tid, (a.B * a.C + 15) >> 4), y);
 }
@@ -779,7 +779,7 @@ hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s) {
 // rows, with the scores S^T = K . Q^T and the output O^T += V^T . P^T of attn_mfma_kernel and a
 // running max and sum per query lane.  The four waves' triples are merged through LDS into the
 // split's partial (unnormalised output, max, sum), which attn_combine_kernel merges over the
-// splits as it does for attn_kernel.
+// splits as it does for attn_row_kernel.
 template <int DH>
 __global__ __launch_bounds__(256) void attn_mfma_chunk_kernel(const AttnArgs a, const int ks) {
   constexpr int KT = 128;       // keys per tile

@@ -637,3 +637,20 @@ def test_imitation_network_on_few_rows(batch, d_model, in_hidden):
     assert dd.sync_status() == (0, 0)
     for s in sorted({0, batch - 1}):
         parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=2)
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+@pytest.mark.parametrize("wl", [synth.S1, synth.S_T5, synth.S_LLAMA], ids=lambda w: w.name)
+def test_nan_scores_reach_the_logits(wl, batch):
+    """A NaN in one query weight of layer 1 makes every attention score of that head NaN: no kernel of
+    the prefill, draft and verify passes turns it back into a number, so every logit is NaN, and the
+    token chosen then is 0."""
+    def plant(w):
+        w["layers"][0]["wq"][3, 5] = np.nan
+
+    dd, dec, pr, z, pt, vt = _setup(wl, seed=41, batch=batch, weights=plant, extra_seq=wl.gamma)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, max_rounds=1)
+    assert dd.sync_status() == (0, 0)
+    r = run.rounds[0]
+    assert np.isnan(run.prefill_logits).all() and np.isnan(r.draft_logits).all() and np.isnan(r.target_logits).all()
+    assert not run.pending0.any() and not r.drafts.any() and not r.targets.any()
