@@ -107,7 +107,7 @@ bool make_layout(const ssd_dims& d, Layout& L, bool allow_fold = true) {
     L.p_x = take(2 * PR * D * 2);
     L.p_attn = take(2 * PR * HD * 2);
     L.p_ffn = take(2 * PR * (size_t)d.d_ff * 2);
-    L.p_inh = take(bf16 ? 2 * ((B + 15) / 16 * 16) * (size_t)d.in_hidden * 2 : 0);
+    L.p_inh = take(bf16 && B > 8 ? 2 * ((B + 15) / 16 * 16) * (size_t)d.in_hidden * 2 : 0);
     L.ssq = take(bf16 ? rows_ssq_floats((int)D, (int)R) * 4 : 0);
     L.attn_part = take((size_t)L.attn_rows * d.n_heads * ATTN_SPLITS_MAX * (d.d_head + 2) * 4);
     L.cur_tok = take(B * 4);
