@@ -578,7 +578,7 @@ def main():
         conf = confidence_sweep(dd, pt, vt, wl, max(1, args.steps // 2), toks_greedy,
                                 dtg / args.steps)
 
-    # prefill alone (its projections on MFMA tiles once the context exceeds the skinny chunk)
+    # prefill alone (its projections on MFMA tiles once the context exceeds the few-row kernel)
     pf_s = prefill_timing(dd, pt, vt)
     pf_flops = prefill_flops(sh, B, wl.prompt_len)
     prefill = {"ms": round(pf_s * 1e3, 3), "tflop": round(pf_flops / 1e12, 4),
