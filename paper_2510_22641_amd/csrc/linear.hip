@@ -563,7 +563,7 @@ hipError_t launch_gemv_t(const LinearArgs& a, hipStream_t s, LaunchTiming* t) {
 
 int argmax_parts_max(int n_out) {
   const int groups = ((n_out + 1) / 2 + GV_WAVES - 1) / GV_WAVES;
-  const int tiles = (n_out + 15) / 16;
+  const int tiles = n_out > 16 ? (n_out + 15) / 16 : 2;  // the many-row kernel: two a column tile
   return groups > tiles ? groups : tiles;
 }
 

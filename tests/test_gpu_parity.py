@@ -654,3 +654,17 @@ def test_nan_scores_reach_the_logits(wl, batch):
     r = run.rounds[0]
     assert np.isnan(run.prefill_logits).all() and np.isnan(r.draft_logits).all() and np.isnan(r.target_logits).all()
     assert not run.pending0.any() and not r.drafts.any() and not r.targets.any()
+
+
+def test_vocabulary_of_one_tile_on_129_rows():
+    """A vocabulary of 12 (less than one tile of features) over a 129-row verify chunk, whose head runs
+    on the many-row kernel with two argmax partials a row: the workspace holds them, and the logits
+    and tokens of the first and last sequence follow the oracle."""
+    from dataclasses import replace
+    wl = synth.S_T5.with_(name="t5-v12", shape=replace(synth.SMALL_T5_BF16, name="t5-v12", vocab=12),
+                          gamma=2, new_tokens=8)
+    dd, dec, pr, z, pt, vt = _setup(wl, seed=43, batch=43, extra_seq=wl.gamma)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, reuse=True, max_rounds=2)
+    assert dd.sync_status() == (0, 0)
+    for s in (0, 42):
+        parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=2)
