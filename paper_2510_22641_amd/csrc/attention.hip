@@ -1006,12 +1006,28 @@ size_t attn_chunk_shm(const AttnArgs& a, int ks) {
   return planes + (size_t)(kfix / a.kv.page_size + 2) * sizeof(int);
 }
 
+// Key splits of a launch with `groups` query blocks per sequence: long self-attention contexts
+// (capacity of 256 keys and more, up to 16 query rows) are split so that about 512 blocks share
+// the keys, at least 128 keys a split.
+int attn_splits(const AttnArgs& a, int groups) {
+  if (a.cross || a.C > 16 || !a.part || a.B * a.C > a.part_rows || a.max_seq < 256) return 1;
+  const int blocks = a.H * a.B * groups;
+  const int want = (512 + blocks - 1) / blocks;
+  const int by_len = (a.max_seq + 127) / 128;
+  int ks = want < by_len ? want : by_len;
+  if (ks > ATTN_SPLITS_MAX) ks = ATTN_SPLITS_MAX;
+  return ks < 1 ? 1 : ks;
+}
+
 // The MFMA chunk attention applies: self-attention of 2..16 rows a sequence over a long float32
 // cache split into ks > 1 key ranges (partials merged by attn_combine_kernel), even pages, no
-// position bias.
+// position bias.  It multiplies bf16 hi / lo halves (about 16 bits), where attn_rows_kernel multiplies
+// float32, so it is kept to launches of few blocks: those split when counted at 8 rows a block (two
+// blocks a sequence past 8 rows: under 256 (head, sequence) pairs there).  Past that it is no faster
+// either: verify of 9 rows of 8 sequences at the LLaMA-7B shape 8.60 ms with it, 8.17 ms without.
 bool attn_chunk_ok(const AttnArgs& a, int ks) {
   if (a.cross || a.C < 2 || a.C > 16 || ks < 2 || a.kvdtype != 0 || a.bias || !a.part ||
-      a.kv.page_size < 2 || (a.dh != 64 && a.dh != 128))
+      attn_splits(a, (a.C + 7) / 8) < 2 || a.kv.page_size < 2 || (a.dh != 64 && a.dh != 128))
     return false;
   const size_t shm = a.dh == 64 ? attn_chunk_shm<64>(a, ks) : attn_chunk_shm<128>(a, ks);
   return shm <= (size_t)156 * 1024;
@@ -1027,19 +1043,6 @@ void launch_attn_chunk(const AttnArgs& a, int ks, hipStream_t s) {
   }
   hipLaunchKernelGGL((attn_mfma_chunk_kernel<DH>), dim3(a.H, a.B, ks), dim3(256),
                      attn_chunk_shm<DH>(a, ks), s, a, ks);
-}
-
-// Key splits of a launch with `groups` query blocks per sequence: long self-attention contexts
-// (capacity of 256 keys and more, up to 16 query rows) are split so that about 512 blocks share
-// the keys, at least 128 keys a split.
-int attn_splits(const AttnArgs& a, int groups) {
-  if (a.cross || a.C > 16 || !a.part || a.B * a.C > a.part_rows || a.max_seq < 256) return 1;
-  const int blocks = a.H * a.B * groups;
-  const int want = (512 + blocks - 1) / blocks;
-  const int by_len = (a.max_seq + 127) / 128;
-  int ks = want < by_len ? want : by_len;
-  if (ks > ATTN_SPLITS_MAX) ks = ATTN_SPLITS_MAX;
-  return ks < 1 ? 1 : ks;
 }
 
 template <typename KT, int DH, int NW, bool CROSS, bool BIAS>

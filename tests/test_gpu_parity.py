@@ -668,3 +668,33 @@ def test_vocabulary_of_one_tile_on_129_rows():
     assert dd.sync_status() == (0, 0)
     for s in (0, 42):
         parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=2)
+
+
+def test_long_float32_cache_keeps_float32_products_past_8_rows():
+    """Verify chunks of 9 rows of 8 sequences over 32 heads and a float32 cache of more than 256
+    positions: 256 (head, sequence) pairs, where attention multiplies float32 and not bf16 halves.  All
+    weights are float32 too and the scores are large (wq and wk scaled: up to about 64), so that halves
+    in the attention show.  A float32 score of 64 dims errs by a few times 64 x 2^-24, and the
+    probabilities and logits with it by as much relatively: 4 x 64 x 2^-24 = 1.5e-5 (measured 2e-6 to
+    4e-6; products of halves without their lo.lo part err by 2^-18: up to 2.4e-4, measured 5e-5)."""
+    from dataclasses import replace
+    sh = replace(synth.SMALL_LLAMA_F32, name="llama-32-heads", n_layers=2, d_model=128, n_heads=32,
+                 d_head=64, d_ff=320, vocab=300, n_visual=9)
+    wl = synth.S_LLAMA_F32.with_(name=sh.name, shape=sh, draft_layers=1, gamma=8, new_tokens=12, deep_scale=1.0)
+
+    def sharpen(w):
+        for lw in w["layers"]:
+            lw["wq"] *= np.float32(20)
+            lw["wk"] *= np.float32(20)
+
+    dd, dec, pr, z, pt, vt = _setup(wl, seed=51, batch=8, weights=sharpen, extra_seq=260)
+    assert dd.cap.max_seq >= 256
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, max_rounds=1)
+    assert dd.sync_status() == (0, 0)
+    for b in (0, 7):
+        r = run.rounds[0]
+        _, (o,) = decode.replay(dec, pr[b], z[b], int(run.pending0[b]), [(r.drafts[b], r.targets[b])], wl.gamma)
+        ref = np.stack(o.target_logits)
+        err = np.linalg.norm(r.target_logits[b] - ref) / np.linalg.norm(ref)
+        print(f"seq {b}: relative error {err:.3g}")
+        assert err <= 1.5e-5
