@@ -435,7 +435,7 @@ __global__ __launch_bounds__(DH) void attn_combine_kernel(const AttnArgs a, cons
       l = fmaf(w, ls[sp], l);
       o = fmaf(w, os[sp], o);
     }
-  const float y = l > 0.f ? o / l : 0.f;
+  const float y = l == 0.f ? 0.f : o / l;  // no key: zeros (a NaN score stays NaN)
   const size_t oi = (size_t)r * HD + h * DH + d;
   if (a.out) a.out[oi] = y;
   if (a.out_planes) store_planes1(a.out_planes + plane_at(r, h * DH + d, (a.B * a.C + 15) >> 4), y);

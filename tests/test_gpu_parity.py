@@ -643,8 +643,8 @@ def test_imitation_network_on_few_rows(batch, d_model, in_hidden):
 @pytest.mark.parametrize("wl", [synth.S1, synth.S_T5, synth.S_LLAMA], ids=lambda w: w.name)
 def test_nan_scores_reach_the_logits(wl, batch):
     """A NaN in one query weight of layer 1 makes every attention score of that head NaN: no kernel of
-    the prefill, draft and verify passes turns it back into a number, so every logit is NaN, and the
-    token chosen then is 0."""
+    the prefill, draft and verify passes over a cache of less than 256 positions (where keys are not
+    split) turns it back into a number, so every logit is NaN, and the token chosen then is 0."""
     def plant(w):
         w["layers"][0]["wq"][3, 5] = np.nan
 
@@ -698,3 +698,24 @@ def test_long_float32_cache_keeps_float32_products_past_8_rows():
         err = np.linalg.norm(r.target_logits[b] - ref) / np.linalg.norm(ref)
         print(f"seq {b}: relative error {err:.3g}")
         assert err <= 1.5e-5
+
+
+@pytest.mark.parametrize("kv", ["f32", "bf16"])
+@pytest.mark.parametrize("wl,batch", [(synth.S1, 1), (synth.S_T5, 1), (synth.S_T5, 3), (synth.S_LLAMA, 1),
+                                      (synth.S_LLAMA_F32, 2)], ids=lambda v: getattr(v, "name", str(v)))
+def test_nan_scores_reach_the_logits_where_keys_are_split(wl, batch, kv):
+    """A NaN in one query weight of layer 1 (as above) over a cache of more than 256 positions, where each
+    head's keys are split over blocks and attn_combine_kernel merges their partials: one-row steps,
+    chunks on the float32 kernel (T5, bf16 cache) and on the bf16-halves kernel (LLaMA, float32 cache)
+    leave every logit NaN."""
+    from paper_2510_22641_amd import runtime
+    w, z, pr = parity.workload_inputs(wl, 41, batch)
+    w["layers"][0]["wq"][3, 5] = np.nan
+    dd = runtime.from_workload(wl, 41, weights=w, max_batch=batch, kv_dtype=kv, extra_seq=260)
+    assert dd.cap.max_seq >= 256
+    pt, vt = dd.upload_inputs(pr, z)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, max_rounds=1)
+    assert dd.sync_status() == (0, 0)
+    r = run.rounds[0]
+    assert np.isnan(run.prefill_logits).all() and np.isnan(r.draft_logits).all() and np.isnan(r.target_logits).all()
+    assert not run.pending0.any() and not r.drafts.any() and not r.targets.any()
