@@ -17,6 +17,7 @@
 #include "kernels.h"
 
 #include <climits>
+#include <type_traits>
 
 namespace ssd {
 
@@ -40,6 +41,45 @@ __device__ __forceinline__ void load_run(const bf16_t* p, float* f) {
     f[4 * u + 2] = __uint_as_float(v.y << 16); f[4 * u + 3] = __uint_as_float(v.y & 0xffff0000u);
   }
 }
+
+// N consecutive value elements in storage form until converted; finite() looks at the exponents alone.
+template <typename KT, int N> struct RawRun;
+template <int N> struct RawRun<float, N> {
+  uint4 r[N / 4];
+  __device__ __forceinline__ void load(const float* p) {
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u) r[u] = reinterpret_cast<const uint4*>(p)[u];
+  }
+  __device__ __forceinline__ float at(int t) const {
+    const uint4& v = r[t / 4];
+    return __uint_as_float(t % 4 == 0 ? v.x : (t % 4 == 1 ? v.y : (t % 4 == 2 ? v.z : v.w)));
+  }
+  __device__ __forceinline__ bool finite() const {
+    uint32_t m = 0;
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u)
+      m = max(m, max(max(r[u].x << 1, r[u].y << 1), max(r[u].z << 1, r[u].w << 1)));
+    return m < 0xff000000u;
+  }
+};
+template <int N> struct RawRun<bf16_t, N> {
+  uint2 r[N / 4];
+  __device__ __forceinline__ void load(const bf16_t* p) {
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u) r[u] = reinterpret_cast<const uint2*>(p)[u];
+  }
+  __device__ __forceinline__ float at(int t) const {
+    const uint32_t w = t % 4 < 2 ? r[t / 4].x : r[t / 4].y;
+    return __uint_as_float(t & 1 ? w & 0xffff0000u : w << 16);
+  }
+  __device__ __forceinline__ bool finite() const {
+    uint32_t m = 0;  // (the upper element's test reads the lower one's bits below its exponent)
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u)
+      m = max(m, max(max(r[u].x << 1, r[u].x << 17), max(r[u].y << 1, r[u].y << 17)));
+    return m < 0xff000000u;
+  }
+};
 
 // One query row of one head: decode steps, and the rows of short chunks.  A block of NW waves per
 // (head, query row [, key split]); wave w takes the 16-key sub-tiles w, w + NW, ...: lane (c = l % 16,
@@ -219,7 +259,7 @@ __global__ __launch_bounds__(64 * NW) void attn_row_kernel(const AttnArgs a, con
 // products and sums throughout, as in a vector kernel.
 // CROSS and BIAS are template parameters so that no branch stands between the first loads.
 template <typename KT, int DH, int NW, bool CROSS, bool BIAS>
-__global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, const int per, const int ks, const uint32_t ps_inv) {
+__global__ __launch_bounds__(64 * NW, NW == 8 && !BIAS && sizeof(KT) == 2 ? 4 : 1) void attn_rows_kernel(const AttnArgs a, const int per, const int ks, const uint32_t ps_inv) {
   constexpr int DQ = DH / 4;   // elements of a key (and query) row per lane
   constexpr int DT = DH / 16;  // output tiles; consecutive value elements per lane
   extern __shared__ __attribute__((aligned(16))) float xo[];  // [NW][DQ + 2][64]
@@ -288,9 +328,13 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, co
 #pragma unroll
   for (int t = 0; t < DT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  for (; t0 < k_end; t0 += 16 * NW) {
+  // one sub-tile; partly: some of its keys are later positions than some of the rows (a constant, or
+  // known at run time)
+  auto tile = [&](auto partly) {
+    constexpr bool whole = std::is_same_v<decltype(partly), std::false_type>;
     bool kok, vok[4];
-    float kf[DQ], vf[4][DT], bv[4];
+    float kf[DQ], bv[4];
+    RawRun<KT, DT> vf[4];
     {
       const KT* kp = row(Kb, t0 + c, kpg, kok) + DQ * g;
       Vec8<KT> r[DQ / 8];
@@ -303,7 +347,7 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, co
     for (int e = 0; e < 4; ++e) {
       const int ki = t0 + 4 * g + e;
       const KT* vp = row(Vb, ki, vpg[e], vok[e]) + DT * c;
-      load_run<DT>(vp, vf[e]);
+      vf[e].load(vp);
       vok[e] = vok[e] && ki < k_end;
       bv[e] = BIAS ? bias[min(max(pq - ki, 0), a.max_seq - 1)] : 0.f;
     }
@@ -318,7 +362,7 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, co
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       // vok: the key is in the context and on a mapped page (a value row and its key row share it)
-      sc[e] = (vok[e] && t0 + 4 * g + e <= pq) ? s0[e] + s1[e] + bv[e] : -INFINITY;
+      sc[e] = (vok[e] && (whole || t0 + 4 * g + e <= pq)) ? s0[e] + s1[e] + bv[e] : -INFINITY;
       mt = fmaxf(mt, sc[e]);
     }
     mt = fmaxf(mt, __shfl_xor(mt, 16, SSD_WAVE));
@@ -335,19 +379,47 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, co
     m_run = m_new;
 #pragma unroll
     for (int t = 0; t < DT; ++t) acc[t] *= alpha;
-    // a value row past the context may hold anything: it enters the products as zeros
+    // A value row past the context may hold anything: it enters the products as zeros.  Among the keys
+    // that only some of the rows see (the block's own later positions), a probability of 0 does not
+    // hide a value that is not finite from the rows before it: such values stay out of the products
+    // too, and the rows that do see one become NaN.
+    if (partly) {
+      bool odd[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) odd[e] = vok[e] && !vf[e].finite();
+      if (__any(odd[0] || odd[1] || odd[2] || odd[3])) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint64_t lanes = __ballot(odd[e]);  // 16 lanes a key
+#pragma unroll
+          for (int kg = 0; kg < 4; ++kg)
+            if (((lanes >> (16 * kg)) & 0xffff) && t0 + 4 * kg + e <= pq) l_run = NAN;
+          vok[e] = vok[e] && !odd[e];
+        }
+      }
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int t = 0; t < DT; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vok[e] ? vf[e][t] : 0.f, sc[e], acc[t], 0, 0, 0);
-    const int tn = t0 + 16 * NW;
-    if (tn < k_end) {
-      kpg = entry(tn + c);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vok[e] ? vf[e].at(t) : 0.f, sc[e], acc[t], 0, 0, 0);
+  };
+  // Keys from base + j0 + 1 on (at most 15, so a wave's last sub-tile) are not seen by every row.  With
+  // 128 dims that sub-tile is code of its own: one body for both held 135 registers and with them one
+  // block a compute unit instead of two (a LLaMA-7B verify of 12 rows 1% slower).  With 64 dims it is
+  // one body, as the second costs its instruction fetches (a FlanT5-xl verify of 72 rows 1% slower).
+  constexpr bool PEEL = !CROSS && DH == 128;
+  while (t0 < (PEEL ? min(k_end, base + j0 - 14) : k_end)) {
+    if constexpr (CROSS || PEEL) tile(std::false_type());
+    else tile(t0 + 15 > base + j0);
+    t0 += 16 * NW;
+    if (t0 < k_end) {
+      kpg = entry(t0 + c);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) vpg[e] = entry(tn + 4 * g + e);
+      for (int e = 0; e < 4; ++e) vpg[e] = entry(t0 + 4 * g + e);
     }
   }
+  if (PEEL && t0 < k_end) tile(std::true_type());
   l_run += __shfl_xor(l_run, 16, SSD_WAVE);
   l_run += __shfl_xor(l_run, 32, SSD_WAVE);
 
@@ -390,7 +462,7 @@ __global__ __launch_bounds__(64 * NW) void attn_rows_kernel(const AttnArgs a, co
     }
     return;
   }
-  const float inv = l > 0.f ? 1.0f / l : 0.f;
+  const float inv = l == 0.f ? 0.f : 1.0f / l;  // no key: zeros (a NaN sum stays NaN)
   const size_t oi = r * HD + h * DH + d0;
 #pragma unroll
   for (int t = 0; t < DT; ++t) o[t] *= inv;

@@ -719,3 +719,35 @@ def test_nan_scores_reach_the_logits_where_keys_are_split(wl, batch, kv):
     r = run.rounds[0]
     assert np.isnan(run.prefill_logits).all() and np.isnan(r.draft_logits).all() and np.isnan(r.target_logits).all()
     assert not run.pending0.any() and not r.drafts.any() and not r.targets.any()
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf], ids=["nan", "inf"])
+@pytest.mark.parametrize("wl,gamma,batch,kv,extra", [
+    (synth.S1, 4, 1, "f32", 0), (synth.S1, 10, 1, "f32", 0), (synth.S_T5, 15, 2, "bf16", 0),
+    (synth.S_T5, 12, 1, "f32", 260), (synth.S_LLAMA, 9, 3, "f32", 0), (synth.S_LLAMA, 15, 1, "bf16", 260),
+    (synth.S_LLAMA_F32, 11, 1, "bf16", 0), (synth.S_T5, 24, 1, "f32", 0)],
+    ids=lambda v: getattr(v, "name", str(v)))
+def test_a_row_that_is_not_finite_leaves_the_rows_before_it_alone(wl, gamma, batch, kv, extra, bad):
+    """A verify chunk whose draft 6 (or 3) is a token with a NaN or Inf embedding: causal rows before
+    it take nothing from its keys and values, so their logits are bit for bit those of the same chunk
+    with an ordinary token in its place; its own row and the rows behind it are NaN."""
+    import torch
+    from paper_2510_22641_amd import runtime
+    wl = wl.with_(gamma=gamma)
+    w, z, pr = parity.workload_inputs(wl, 61, batch)
+    tok, at = 77, min(6, gamma - 1)
+    w["embed"][tok, 5] = bad
+    assert not (pr == tok).any()
+    dd = runtime.from_workload(wl, 61, weights=w, max_batch=batch, kv_dtype=kv, extra_seq=extra)
+    pt, vt = dd.upload_inputs(pr, z)
+    pending, _ = dd.prefill(pt, vt)
+    assert not (pending == tok).any()
+    draft = dd.buf("forced", (batch, gamma))
+    draft.copy_((torch.arange(batch * gamma, device=draft.device) % 70).view(batch, gamma))
+    clean = dd.verify(pending, draft, gamma, logits=True)[1].cpu().numpy().copy()
+    draft[:, at - 1] = tok
+    dirty = dd.verify(pending, draft, gamma, logits=True)[1].cpu().numpy().copy()
+    assert dd.sync_status() == (0, 0)
+    assert np.isfinite(clean).all()
+    assert np.array_equal(dirty[:, :at], clean[:, :at])
+    assert np.isnan(dirty[:, at:]).all()
