@@ -42,6 +42,7 @@ struct Layout {
   int kpart_max = 0;  // K-range partials of the long row blocks' residual projections
   bool fold = false;  // the folded cross-attention matrices are carved (fold_q, fold_o)
   bool fg = false;    // and the scores-from-the-layer-input matrices of layers 1..k (fold_fg)
+  bool inh_planes = false;  // the imitation network's hidden features as planes (p_inh)
 };
 
 int ctx_len_max(const ssd_dims& d) {
@@ -72,8 +73,10 @@ bool fold_fg_ok(const ssd_dims& d) {
 
 // Workspace layout: the scratch a chain of launches writes (residual rows, projections, operand
 // planes, argmax partials, the layer-k stash ...), the tables, the folded cross-attention and
-// the loop state of ssd_generate, each slice 256-byte aligned.
-bool make_layout(const ssd_dims& d, Layout& L, bool allow_fold = true) {
+// the loop state of ssd_generate, each slice 256-byte aligned.  Without allow_fold the
+// cross-attention stays unfolded; without allow_inh the imitation network's hidden features stay
+// float32 rows for any batch.
+bool make_layout(const ssd_dims& d, Layout& L, bool allow_fold = true, bool allow_inh = true) {
   const size_t B = d.max_batch, G = d.max_gamma, D = d.d_model, HD = (size_t)d.n_heads * d.d_head;
   L.ctx_max = ctx_len_max(d);
   size_t rows = B * (G + 1);
@@ -107,7 +110,8 @@ bool make_layout(const ssd_dims& d, Layout& L, bool allow_fold = true) {
     L.p_x = take(2 * PR * D * 2);
     L.p_attn = take(2 * PR * HD * 2);
     L.p_ffn = take(2 * PR * (size_t)d.d_ff * 2);
-    L.p_inh = take(bf16 && B > 8 ? 2 * ((B + 15) / 16 * 16) * (size_t)d.in_hidden * 2 : 0);
+    L.inh_planes = bf16 && B > 8 && allow_inh;
+    L.p_inh = take(L.inh_planes ? 2 * ((B + 15) / 16 * 16) * (size_t)d.in_hidden * 2 : 0);
     L.ssq = take(bf16 ? rows_ssq_floats((int)D, (int)R) * 4 : 0);
     L.attn_part = take((size_t)L.attn_rows * d.n_heads * ATTN_SPLITS_MAX * (d.d_head + 2) * 4);
     L.cur_tok = take(B * 4);
@@ -520,7 +524,7 @@ int run_imitation(ssd_ctx* c, const float* xk, int B, F between) {
   a.w[0] = c->w.in_w1; a.n_per = d.in_hidden; a.epi = EPI_BIAS_GELU; a.bias = c->w.in_b1;
   a.y = inh; a.ldy = d.in_hidden;
   // more than 8 rows with bf16 weights: on planes of the normalised rows and of the hidden features
-  const bool planes = B > 8 && d.wdtype == SSD_BF16;
+  const bool planes = B > 8 && c->L.inh_planes;
   bf16_t* p_inh = c->at<bf16_t>(c->L.p_inh);
   if (planes) {
     bf16_t* p_x = c->at<bf16_t>(c->L.p_x);
@@ -914,6 +918,8 @@ int ssd_create_static(const ssd_dims* dims, const ssd_weights* w, const ssd_kv* 
   if (rc) return rc;
   Layout L;
   make_layout(*dims, L, /*allow_fold=*/false);
+  // the planes of a wide imitation network on a large batch may not fit; its float32 rows may
+  if (L.total > SSD_STATIC_SCRATCH_BYTES) make_layout(*dims, L, /*allow_fold=*/false, /*allow_inh=*/false);
   if (L.total > SSD_STATIC_SCRATCH_BYTES) return SSD_ERR_CAPACITY;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0) return SSD_ERR_HIP;

@@ -110,3 +110,24 @@ def test_static_context_refusals():
     dd.close()
     dd2.create(static=True)  # free again once the first is destroyed
     dd2.close()
+
+
+def test_static_context_of_a_wide_imitation_network_on_a_large_batch():
+    """256 sequences with an imitation network of 16384 features: its hidden features as operand planes
+    (16 MiB) would take the workspace past the fixed array, so a static context keeps them as float32
+    rows and is accepted; drafts and verify follow the oracle."""
+    from dataclasses import replace
+    from paper_2510_22641_amd import runtime, ssd as abi
+    sh = replace(synth.SMALL_LLAMA_BF16, name="llama-wide-imitation", n_layers=2, d_model=64, n_heads=1,
+                 d_head=64, d_ff=128, vocab=8000, n_visual=2, in_hidden=16384)
+    wl = synth.S_LLAMA.with_(name=sh.name, shape=sh, prompt_len=4, draft_layers=1, gamma=8, new_tokens=6)
+    w, z, pr = parity.workload_inputs(wl, 81, 256)
+    dd = runtime.from_workload(wl, 81, weights=w, max_batch=256, static=True)
+    assert abi.ssd_workspace_bytes(dd.dims()) > abi.SSD_STATIC_SCRATCH_BYTES
+    pt, vt = dd.upload_inputs(pr, z)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, reuse=True, max_rounds=1)
+    assert dd.sync_status() == (0, 0)
+    dd.close()
+    dec = Decoder(wl.shape, w, wl.draft_layers)
+    for b in (0, 9, 255):
+        parity.check_run_against_oracle(dec, wl.shape, pr[b], z[b], run, b, wl.gamma, max_rounds=1)
