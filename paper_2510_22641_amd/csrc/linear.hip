@@ -30,7 +30,7 @@ namespace {
 // elements of both rows; the whole row for K <= 6144) at once and the many resident waves of a CU
 // hide the memory latency.
 // RMSNorm is folded: LDS holds gain * x and the per-row 1/rms multiplies the dot products in the
-// epilogue; LayerNorm inputs are normalised while staged.
+// epilogue; LayerNorm inputs are staged as they are and normalised in place.
 // (The wave index goes through readfirstlane in these kernels so that the compiler treats the
 // wave's row choice as uniform: the matrix pointers then come from scalar registers instead of
 // vector loads of the argument buffer that would wait for the inputs.)
@@ -57,45 +57,60 @@ __global__ __launch_bounds__(256) void gemv_kernel(const LinearArgs a) {
 #pragma unroll
   for (int m = 0; m < MB; ++m) p2[m] = 0.f;
   if (ln) {
-    // LayerNorm: statistics first, then the normalised rows
-    float p1[MB];
+    // LayerNorm: the rows as they are and their means, the variances about the means (mean square
+    // less squared mean would cancel where the mean is large against the spread), then the normalised
+    // rows; a thread meets its own elements again
+    auto row_sums = [&]() {
 #pragma unroll
-    for (int m = 0; m < MB; ++m) p1[m] = 0.f;
-    for (int idx = tid * 4; idx < MB * ldxs; idx += 1024) {
-      const int m = idx / ldxs, k = idx - m * ldxs;
-      if (m < mrows && k < K) {
-        const float4 v = *reinterpret_cast<const float4*>(a.x + (size_t)(m0 + m) * a.ldx + k);
+      for (int m = 0; m < MB; ++m) p2[m] = wave_sum(p2[m]);
+      if (lane == 0) {
 #pragma unroll
-        for (int mm = 0; mm < MB; ++mm)
-          if (mm == m) {
-            p1[mm] += (v.x + v.y) + (v.z + v.w);
-            p2[mm] += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-          }
+        for (int m = 0; m < MB; ++m) red[wave][m] = p2[m];
       }
-    }
-#pragma unroll
-    for (int m = 0; m < MB; ++m) { p1[m] = wave_sum(p1[m]); p2[m] = wave_sum(p2[m]); }
-    if (lane == 0) {
-#pragma unroll
-      for (int m = 0; m < MB; ++m) { red[wave][2 * m] = p1[m]; red[wave][2 * m + 1] = p2[m]; }
-    }
-    __syncthreads();
+      __syncthreads();
+    };
+    auto total = [&](int m) { return (red[0][m] + red[1][m]) + (red[2][m] + red[3][m]); };
     for (int idx = tid * 4; idx < MB * ldxs; idx += 1024) {
       const int m = idx / ldxs, k = idx - m * ldxs;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (m < mrows && k < K) {
-        const float s1 = (red[0][2 * m] + red[1][2 * m]) + (red[2][2 * m] + red[3][2 * m]);
-        const float s2 = (red[0][2 * m + 1] + red[1][2 * m + 1]) + (red[2][2 * m + 1] + red[3][2 * m + 1]);
-        const float mean = s1 / (float)K;
-        const float rstd = 1.0f / sqrtf(fmaxf(s2 / (float)K - mean * mean, 0.f) + a.eps);
-        v = *reinterpret_cast<const float4*>(a.x + (size_t)(m0 + m) * a.ldx + k);
-        const float4 g = *reinterpret_cast<const float4*>(a.gain + k);
-        const float4 b = *reinterpret_cast<const float4*>(a.shift + k);
-        v.x = (v.x - mean) * rstd * g.x + b.x;
-        v.y = (v.y - mean) * rstd * g.y + b.y;
-        v.z = (v.z - mean) * rstd * g.z + b.z;
-        v.w = (v.w - mean) * rstd * g.w + b.w;
-      }
+      if (m < mrows && k < K) v = *reinterpret_cast<const float4*>(a.x + (size_t)(m0 + m) * a.ldx + k);
+#pragma unroll
+      for (int mm = 0; mm < MB; ++mm)
+        if (mm == m) p2[mm] += (v.x + v.y) + (v.z + v.w);
+      *reinterpret_cast<float4*>(xs + m * ldxs + xs_off(k, ldxs)) = v;
+    }
+    row_sums();
+    float mean[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      mean[m] = total(m) / (float)K;
+      p2[m] = 0.f;
+    }
+    __syncthreads();  // the means are read before the next sums take their place
+    for (int idx = tid * 4; idx < MB * ldxs; idx += 1024) {
+      const int m = idx / ldxs, k = idx - m * ldxs;
+      if (k >= K) continue;
+      float4 v = *reinterpret_cast<const float4*>(xs + m * ldxs + xs_off(k, ldxs));
+#pragma unroll
+      for (int mm = 0; mm < MB; ++mm)
+        if (mm == m) {
+          v.x -= mean[mm]; v.y -= mean[mm]; v.z -= mean[mm]; v.w -= mean[mm];
+          p2[mm] += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+        }
+      *reinterpret_cast<float4*>(xs + m * ldxs + xs_off(k, ldxs)) = v;
+    }
+    row_sums();
+    for (int idx = tid * 4; idx < MB * ldxs; idx += 1024) {
+      const int m = idx / ldxs, k = idx - m * ldxs;
+      if (k >= K) continue;
+      const float rstd = 1.0f / sqrtf(total(m) / (float)K + a.eps);
+      float4 v = *reinterpret_cast<const float4*>(xs + m * ldxs + xs_off(k, ldxs));
+      const float4 g = *reinterpret_cast<const float4*>(a.gain + k);
+      const float4 b = *reinterpret_cast<const float4*>(a.shift + k);
+      v.x = v.x * rstd * g.x + b.x;
+      v.y = v.y * rstd * g.y + b.y;
+      v.z = v.z * rstd * g.z + b.z;
+      v.w = v.w * rstd * g.w + b.w;
       *reinterpret_cast<float4*>(xs + m * ldxs + xs_off(k, ldxs)) = v;
     }
   } else {
@@ -414,29 +429,40 @@ __global__ __launch_bounds__(64 * SKW) void dense_rows_kernel(const LinearArgs a
   __builtin_amdgcn_sched_barrier(0);
 
   if constexpr (LN) {
+    // mean, then the variance about it (mean square less squared mean would cancel where the mean is
+    // large against the spread)
     float p1 = 0.f, p2 = 0.f;
 #pragma unroll
     for (int u = 0; u < SK; ++u) {
       if (s_beg + u >= s_end) break;  // the same for the whole wave
 #pragma unroll
+      for (int e = 0; e < 8; ++e) p1 += xv[u][e >> 2][e & 3];
+    }
+#pragma unroll
+    for (int o = 8; o < SSD_WAVE; o <<= 1) p1 += __shfl_xor(p1, o, SSD_WAVE);
+    if (lane < 8) st[wave][0][lane] = p1;
+    __syncthreads();
+    p1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < SKW; ++w) p1 += st[w][0][lane & 7];
+    const float mean = p1 / (float)K;
+#pragma unroll
+    for (int u = 0; u < SK; ++u) {
+      if (s_beg + u >= s_end) break;
+#pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float v = xv[u][e >> 2][e & 3];
-        p1 += v;
-        p2 += v * v;
+        const float v = xv[u][e >> 2][e & 3] - mean;
+        p2 = fmaf(v, v, p2);
       }
     }
 #pragma unroll
-    for (int o = 8; o < SSD_WAVE; o <<= 1) {
-      p1 += __shfl_xor(p1, o, SSD_WAVE);
-      p2 += __shfl_xor(p2, o, SSD_WAVE);
-    }
-    if (lane < 8) { st[wave][0][lane] = p1; st[wave][1][lane] = p2; }
+    for (int o = 8; o < SSD_WAVE; o <<= 1) p2 += __shfl_xor(p2, o, SSD_WAVE);
+    if (lane < 8) st[wave][1][lane] = p2;
     __syncthreads();
-    p1 = p2 = 0.f;
+    p2 = 0.f;
 #pragma unroll
-    for (int w = 0; w < SKW; ++w) { p1 += st[w][0][lane & 7]; p2 += st[w][1][lane & 7]; }
-    const float mean = p1 / (float)K;
-    const float rstd = 1.0f / sqrtf(fmaxf(p2 / (float)K - mean * mean, 0.f) + a.eps);
+    for (int w = 0; w < SKW; ++w) p2 += st[w][1][lane & 7];
+    const float rstd = 1.0f / sqrtf(p2 / (float)K + a.eps);
 #pragma unroll
     for (int u = 0; u < SK; ++u)
 #pragma unroll

@@ -751,3 +751,30 @@ def test_a_row_that_is_not_finite_leaves_the_rows_before_it_alone(wl, gamma, bat
     assert np.isfinite(clean).all()
     assert np.array_equal(dirty[:, :at], clean[:, :at])
     assert np.isnan(dirty[:, at:]).all()
+
+
+@pytest.mark.parametrize("batch,d_model", [(1, 320), (1, 2112), (2, 320), (8, 2112), (3, 4160), (9, 320)],
+                         ids=lambda v: str(v))
+def test_imitation_network_on_rows_far_from_zero(batch, d_model):
+    """Draft steps on residual rows of 512 but for one element, the token's, at 510: their mean is some
+    thousand times their spread.  A LayerNorm variance taken as mean square less squared mean is lost
+    in float32 there (512^2 2^-24 = 0.016 against 4 / d_model); taken about the mean it is not, so
+    drafts of 1, 2, 3, 8 and 9 rows (the one-row, vector, few-row and plane kernels) follow the oracle
+    alike.  (The draft layer adds nothing and the network has no residual: its input is the embedding
+    and the logits are its output's.)"""
+    from dataclasses import replace
+    sh = replace(synth.SMALL_T5_BF16, name="t5-offset", n_layers=2, d_model=d_model, n_heads=2, d_head=64,
+                 d_ff=320, vocab=300, in_residual=False)
+    wl = synth.S_T5.with_(name=sh.name, shape=sh, draft_layers=1, gamma=2, new_tokens=8)
+
+    def offset(w):
+        w["embed"][:] = 512
+        w["embed"][np.arange(300), np.arange(300)] = 510
+        for n in ("wo", "xo", "w_down"):
+            w["layers"][0][n][:] = 0
+
+    dd, dec, pr, z, pt, vt = _setup(wl, seed=71, batch=batch, weights=offset, extra_seq=wl.gamma)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, reuse=True, max_rounds=1)
+    assert dd.sync_status() == (0, 0)
+    for s in sorted({0, batch - 1}):
+        parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=1)
