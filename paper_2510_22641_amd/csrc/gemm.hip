@@ -257,9 +257,14 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
     for (int q = 0; q < PW; ++q) {
       const bool plane = wave * PW + q < AP;
       const char* p = src[q] + (size_t)kt * (plane ? (size_t)ng * (PLANE_FRAG * 2 * KB) : (size_t)(RK * 2));
-      // LDS-direct load: lane l's 16 bytes land at M0 + 16 l (one wait state after the M0 write)
+      // LDS-direct load: lane l's 16 bytes land at M0 + 16 l (one wait state after the M0 write).  (The
+      // compiler reserves M0, so it warns of the clobber; it is named all the same, so that no value
+      // of its own is expected to live there across the statement.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :: "s"(st + q * 1024), "v"(off[q]), "s"(p) : "memory");
+                   :: "s"(st + q * 1024), "v"(off[q]), "s"(p) : "memory", "m0");
+#pragma clang diagnostic pop
     }
   };
 #pragma unroll
