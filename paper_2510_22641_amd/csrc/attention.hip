@@ -6,13 +6,18 @@
 // for LLaMA, scaled by 1/sqrt(dh) with q and k already rotated.  Cross-attention (T5): all n_keys
 // visual keys, no mask, no bias, no scale.
 //
-// One block per (head, sequence, query row) for single rows and short-context chunks of up to 16
-// rows, else per (head, sequence, 8 query rows); long contexts split each head's keys over several
-// blocks whose partials attn_combine_kernel merges.  Every thread issues its key row and its
-// first value chunks before the first barrier (they do not depend on the scores); scores for the
-// live rows go to LDS, one wave per row turns them into softmax numerators, and P.V splits the
-// keys over all threads (16-byte value chunks, 8 loads in flight per thread) with a shuffle + LDS
-// reduction.  Bound: bytes of K and V read (HBM/L2) and one or two memory round trips.
+//  * attn_row_kernel - one query row a block: decode steps, and the rows of short chunks over short
+//    contexts.  Vector products in float32.
+//  * attn_rows_kernel - 16 query rows a block on the float32 matrix instruction: longer chunks, T5 and
+//    bf16-cache prefills.
+//  * attn_mfma_kernel - 64 query rows a block on bf16 hi / lo halves: prefills without a position bias
+//    over a float32 cache.
+//  * attn_mfma_chunk_kernel - one key split of a chunk of up to 16 rows on bf16 hi / lo halves: long
+//    float32 caches without a position bias, launches of few (head, sequence) pairs.
+// Steps and chunks of up to 16 rows over a capacity of 256 keys and more split each head's keys over
+// several blocks, whose partials attn_combine_kernel merges.  In every kernel a wave keeps a running
+// maximum and sum over its keys (no row of scores is held), and the waves' results meet in LDS once.
+// Bound: bytes of K and V read (HBM / L2) and one or two memory round trips.
 #include "device.h"
 #include "kernels.h"
 
@@ -249,7 +254,7 @@ __global__ __launch_bounds__(64 * NW) void attn_row_kernel(const AttnArgs a, con
 }
 
 // Attention of 16 query rows of one head on float32 matrix products (v_mfma_f32_16x16x4_f32), for
-// single rows, verify chunks and prefill blocks, paged or cross, float32 or bf16 keys.  One block
+// verify chunks and prefill blocks, paged or cross, float32 or bf16 keys.  One block
 // of NW waves per (head, sequence, 16 rows [, key split]); wave w takes the 16-key sub-tiles
 // w, w + NW, ... of the block's keys, straight from memory into registers: lane (c = l % 16,
 // g = l / 16) loads a quarter (dims DQ g ..) of key c and of query c, so that S^T = K . Q^T runs
@@ -820,7 +825,7 @@ size_t attn_mfma_shm(const AttnArgs& a) {
 }
 
 // The MFMA prefill attention applies: self-attention of more than 16 rows a sequence over a
-// float32 cache whose pages hold 2..64 keys dividing 64, no position bias, no output planes.
+// float32 cache whose pages hold 2..64 keys dividing 64, no position bias.
 bool attn_mfma_ok(const AttnArgs& a) {
   if (a.cross || a.C <= 16 || a.kvdtype != 0 || a.bias || a.kv.page_size < 2 ||
       64 % a.kv.page_size || (a.dh != 64 && a.dh != 128))

@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256, 2) void gemm_ring_kernel(const LinearArgs a) {
     constexpr int TP = 256 / BM;  // threads per row
     const int row = tid / TP, p0 = tid % TP, m = min(m0 + row, M - 1);
     float s2 = 0.f;
-    for (int p = p0; p < a.in_nssq; p += 16 * TP) {  // 16 requested together (up to 128 partials a row)
+    for (int p = p0; p < a.in_nssq; p += 16 * TP) {  // 16 requested together
       float v[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) v[u] = a.in_ssq[(size_t)min(p + u * TP, a.in_nssq - 1) * ssq_ld + m];

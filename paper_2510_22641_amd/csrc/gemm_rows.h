@@ -60,7 +60,8 @@ enum GrMode { GR_FULL = 0, GR_PACK = 1, GR_HALF = 2 };
 // 16-byte loads a lane and step of the weights and of the planes
 constexpr int gr_wloads(int mode, int nt) { return mode == GR_HALF ? nt : 2 * nt; }
 constexpr int gr_aloads(int mode, int rg) { return mode == GR_FULL ? 4 * rg : 2; }
-// registers of two one-step batches and the accumulators within a wave's share
+// registers of two one-step batches and the accumulators within a wave's share (QKV's addresses and
+// rotary factors come on top: of 4 tiles and 2 groups it spills three registers)
 constexpr bool gr_fits(int nt, int rg) { return 16 * (nt + 2 * rg) + 4 * nt * rg <= 170; }
 // steps a batch that two batches' registers hold, and that one's hold
 constexpr int gr_batch(int mode, int nt, int rg) {

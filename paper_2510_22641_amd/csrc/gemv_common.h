@@ -1,6 +1,7 @@
-// Device helpers of the weight-streaming GEMV kernels (linear.hip): row-pair
-// addressing of the concatenated / gated matrices, the QKV epilogue (rotary and the paged KV
-// store), and the fused epilogues of the vector path for up to MB input rows.
+// Device helpers of the linear-layer kernels: row-pair addressing of the concatenated / gated
+// matrices and the fused epilogues for up to MB input rows of the weight-streaming GEMVs (gemv1.hip,
+// linear.hip), and what the kernels of gemm.hip and gemm_rows.h share with them: the choice of a
+// matrix, the gated activation, the QKV store (rotary and the paged KV cache).
 #pragma once
 
 #include "device.h"

@@ -12,7 +12,7 @@ namespace ssd {
 
 // Input transform of a linear layer: none, RMSNorm (gain), LayerNorm (gain, shift), or a softmax
 // over consecutive groups of LinearArgs::group inputs (the folded cross-attention's probabilities;
-// one-row vector path only).
+// one-row kernels and launch_fold_rows only).
 enum Norm { NORM_NONE = 0, NORM_RMS = 1, NORM_LN = 2, NORM_SOFTMAX = 3 };
 
 // Paged KV addressing shared by the QKV epilogue and the attention kernels.
@@ -39,7 +39,7 @@ enum Epi {
                        // keys (even entries) and values (odd) of every layer into their caches
                        // (launch_linear_rows only)
   EPI_QKV = 7          // w = (wq, wk, wv): rotary on q and k (when rope_cos is set), q -> y[m][.],
-                       // k and v into the paged pools at the row's position (vector path only)
+                       // k and v into the paged pools at the row's position
 };
 
 // y = epilogue( W . norm(x) ) for M rows.  The output features are up to three matrices of
@@ -135,7 +135,7 @@ struct LaunchTiming {
 // Compute units of the current device.
 int cu_count();
 
-// Pieces per batch (the KP of gemv_kernel) the vector path uses for rows of K elements.
+// Pieces per batch (the KP of gemv1_kernel and gemv_kernel) for rows of K elements.
 int gemv_pieces(int K);
 
 // Launch y = epilogue(W . norm(x)).  For EPI_ARGMAX, *n_parts receives the number of partials

@@ -1,14 +1,15 @@
 // Linear layers y = epilogue(W . norm(x)) for the decoder, the imitation network and the LM head.
 //
 // Paths:
-//  * gemv_kernel — weight streaming for 2..8 rows in float32 (or rows longer than a batch): the
-//    input rows are staged in LDS with the gain applied, one row pair per wave.
+//  * gemv_kernel — weight streaming in blocks of up to 8 float32 rows: float32 weights, the
+//    imitation network's rows that dense_rows_kernel does not take, single rows past the limits of
+//    gemv1.hip.  The input rows are staged in LDS with the gain applied, one row pair per wave.
+//  * dense_rows_kernel — the imitation network on 2..8 rows (bf16 weights, rows up to 4096) on the
+//    float32 matrix instruction.
 //  * fold_rows_kernel — 2..8 rows of the folded cross-attention (float32 matrices) on matrix
 //    products of bf16 hi / lo splits.
-//
-// Two rows and more with bf16 weights take the kernels of gemm.hip.
-//
-// One row takes the kernels of gemv1.hip.
+// One row takes the kernels of gemv1.hip, the decoder's layers on two rows and more with bf16
+// weights those of gemm.hip.
 //
 // Every path accumulates in fp32 and ends in a fused epilogue (store, residual (+ stash), gated
 // activation, bias + GELU, bias + residual, per-block (max, argmax) partials for the LM head, or

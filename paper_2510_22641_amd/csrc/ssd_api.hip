@@ -166,7 +166,8 @@ bool dims_ok(const ssd_dims* d) {
   if (d->kvdtype != SSD_F32 && d->kvdtype != SSD_BF16) return false;
   if (d->max_batch < 1 || d->max_batch > 256) return false;
   if (d->max_gamma < 0 || d->max_gamma > 32) return false;
-  if (d->max_seq < 2 || d->max_seq > 1024) return false;  // attention keeps rows of scores in LDS
+  // (1024: the longest cache the attention kernels are tested with; their page arithmetic holds to 2^15)
+  if (d->max_seq < 2 || d->max_seq > 1024) return false;
   if (d->max_prompt < 1 || d->page_size < 1 || d->max_pages < 1) return false;
   if ((long long)d->max_pages * d->page_size < d->max_seq) return false;
   if (ctx_len_max(*d) > d->max_seq) return false;
@@ -324,7 +325,7 @@ int run_layers(ssd_ctx* c, float* x, int B, int C, int pos_off, int l0, int l1, 
   bf16_t* p_ffn = c->at<bf16_t>(c->L.p_ffn);
   float* ssq = c->at<float>(c->L.ssq);
   int nssq = 1;  // partials behind the current p_x
-  // one linear layer: the plane path, else the vector path on float32 rows
+  // one linear layer: on planes, else on float32 rows (the one-row and vector kernels)
   auto linear = [&](LinearArgs& a, const bf16_t* in) -> hipError_t {
     if (!planes) return run_linear(c, a);
     a.in_planes = in;
