@@ -20,7 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssd.so")
-SOURCES = ["linear.hip", "gemv1.hip", "gemm.hip", "gemm_rows_store.hip", "gemm_rows_store_rms.hip",
+SOURCES = ["linear.hip", "gemv1.hip", "gemm.hip", "gemm_rows_bias.hip", "gemm_rows_store_rms.hip",
            "gemm_rows_resid.hip", "gemm_rows_qkv.hip", "gemm_rows_gated.hip",
            "gemm_rows_argmax.hip", "gemm_rows_cross.hip",
            "attention.hip", "misc.hip", "sample.hip", "ssd_api.hip"]

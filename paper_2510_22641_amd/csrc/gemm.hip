@@ -548,11 +548,11 @@ struct RingForm {
   int mi, nj, kb, ns, fit;
   double us[4];
 };
-constexpr RingForm RING_FORMS[6] = {
+constexpr RingForm RING_FORMS[5] = {
     {4, 8, 1, 2, 2, {1.0, 1.42, 0, 0}},      // 128 x 256
     {4, 4, 1, 2, 3, {0.61, 0.85, 1.27, 0}},  // 128 x 128
-    {2, 4, 1, 2, 4, {0.49, 0.58, 0.87, 1.1}},  // 64 x 128, two stages
-    {2, 4, 1, 4, 2, {0.36, 0.52, 0, 0}},     // 64 x 128, four stages
+    {2, 4, 1, 4, 2, {0.36, 0.52, 0, 0}},     // 64 x 128, four stages (with two stages, and four blocks a unit,
+                                             // it never was the cheapest)
     {2, 2, 2, 2, 3, {0.31, 0.40, 0.50, 0}},  // 64 x 64, steps of 64
     {2, 2, 1, 4, 3, {0.25, 0.38, 0.51, 0}},  // 64 x 64, four stages
 };
@@ -566,7 +566,7 @@ RingShape ring_shape(int width, int M, int K, bool can_split, int kpart_max) {
   const int cus = cu_count(), steps = K / 32;
   RingShape best = {0, 1};
   double best_t = -1.0;
-  for (int f = 0; f < 6; ++f) {
+  for (int f = 0; f < 5; ++f) {
     const RingForm& rf = RING_FORMS[f];
     const long long tiles = (long long)((M + 32 * rf.mi - 1) / (32 * rf.mi)) * ((width + 32 * rf.nj - 1) / (32 * rf.nj));
     for (int S = 1; S <= (can_split ? (kpart_max < 4 ? kpart_max : 4) : 1); ++S) {
@@ -610,8 +610,7 @@ hipError_t launch_ring(const LinearArgs& a, int form, int n_out, hipStream_t s) 
     case 1: return launch_ring_t<KIND, 1>(a, n_out, s);
     case 2: return launch_ring_t<KIND, 2>(a, n_out, s);
     case 3: return launch_ring_t<KIND, 3>(a, n_out, s);
-    case 4: return launch_ring_t<KIND, 4>(a, n_out, s);
-    default: return launch_ring_t<KIND, 5>(a, n_out, s);
+    default: return launch_ring_t<KIND, 4>(a, n_out, s);
   }
 }
 
@@ -663,13 +662,13 @@ hipError_t launch_linear_rows(const LinearArgs& args, hipStream_t s, int* n_part
     if (n_ssq) *n_ssq = blocks;
     const bool rms = b.norm == NORM_RMS;
     if (cross) return launch_rows_cross(b, sh, blocks, s);
-    if (b.epi == EPI_STORE) return rms ? launch_rows_store_rms(b, sh, blocks, s) : launch_rows_store(b, sh, blocks, s);
-    if (rms != (gated || b.epi == EPI_QKV || b.epi == EPI_ARGMAX)) return hipErrorInvalidValue;
+    if (rms != (b.epi == EPI_STORE || gated || b.epi == EPI_QKV || b.epi == EPI_ARGMAX)) return hipErrorInvalidValue;
+    if (b.epi == EPI_STORE) return launch_rows_store_rms(b, sh, blocks, s);
     if (b.epi == EPI_RESID) return launch_rows_resid(b, sh, blocks, s);
     if (b.epi == EPI_QKV) return launch_rows_qkv(b, sh, blocks, s);
     if (gated) return launch_rows_gated(b, sh, blocks, s);
     if (b.epi == EPI_ARGMAX) return launch_rows_argmax(b, sh, blocks, s);
-    return launch_rows_store(b, sh, blocks, s);
+    return launch_rows_bias(b, sh, blocks, s);
   }
   const bool vec = b.epi == EPI_ARGMAX || (n_out % 8 == 0 && b.n_per % 4 == 0);
   if (!vec) return hipErrorInvalidValue;

@@ -15,7 +15,7 @@ struct RowsShape {
   int mode, nt, rg;
 };
 
-hipError_t launch_rows_store(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
+hipError_t launch_rows_bias(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 hipError_t launch_rows_store_rms(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 hipError_t launch_rows_resid(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
 hipError_t launch_rows_qkv(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s);
@@ -74,7 +74,7 @@ constexpr int gr_one(int mode, int nt, int rg) {
 
 // The epilogue is a template parameter: with no branch on it ahead of the first loads, every load
 // of the prologue goes out in one burst instead of waiting for the branches' arguments in turn.
-enum GrKind { GR_STORE = 0, GR_STORE_RMS, GR_RESID, GR_QKV, GR_GATED, GR_ARGMAX, GR_CROSS };
+enum GrKind { GR_BIAS = 0, GR_STORE_RMS, GR_RESID, GR_QKV, GR_GATED, GR_ARGMAX, GR_CROSS };
 
 // ONE: a wave's share of K fits one batch (everything it reads is in flight at once).  ONCE: one row
 // block, so each weight is read by one block only and need not stay in the caches (at 12 rows of the
@@ -386,11 +386,11 @@ __global__ __launch_bounds__(64 * GR_WAVES) void gemv_rows_kernel(const LinearAr
         if (a.out_planes)
           store_planes1(a.out_planes + plane_at(tg, n, ng), a.out_gain ? (pre ? gain : a.out_gain[n]) * t : t);
         y2 = fmaf(t, t, y2);
-      } else if (!rms && a.epi == EPI_BIAS_GELU) {
+      } else if (KIND == GR_BIAS && a.epi == EPI_BIAS_GELU) {
         const float t = gelu_tanh(v + a.bias[n]);
         *yp = t;
         if (a.out_planes) store_planes1(a.out_planes + plane_at(tg, n, ng), t);
-      } else if (!rms && a.epi == EPI_BIAS_RESID) {
+      } else if (KIND == GR_BIAS) {
         *yp = (a.resid ? a.resid[(size_t)tg * a.ldr + n] : 0.f) + (v + a.bias[n]);
       } else {
         *yp = v;
@@ -455,8 +455,13 @@ hipError_t launch_rows_t(const LinearArgs& a, int blocks, hipStream_t s) {
 
 template <int KIND, int NT>
 hipError_t launch_rows_nt(const LinearArgs& a, RowsShape sh, int blocks, hipStream_t s) {
-  if (sh.mode == GR_PACK) return launch_rows_t<KIND, GR_PACK, NT, 1>(a, blocks, s);
-  if constexpr (NT == 1 && KIND <= GR_RESID) if (sh.mode == GR_HALF) return launch_rows_t<KIND, GR_HALF, 1, 1>(a, blocks, s);
+  if constexpr (KIND == GR_BIAS) {  // the imitation network past 8 rows
+    if (sh.mode != GR_FULL) return hipErrorInvalidValue;
+  } else {
+    if (sh.mode == GR_PACK) return launch_rows_t<KIND, GR_PACK, NT, 1>(a, blocks, s);
+    if constexpr (NT == 1 && (KIND == GR_STORE_RMS || KIND == GR_RESID))
+      if (sh.mode == GR_HALF) return launch_rows_t<KIND, GR_HALF, 1, 1>(a, blocks, s);
+  }
   if (sh.rg == 1) return launch_rows_t<KIND, GR_FULL, NT, 1>(a, blocks, s);
   if constexpr (gr_fits(NT, 2)) if (sh.rg == 2) return launch_rows_t<KIND, GR_FULL, NT, 2>(a, blocks, s);
   if constexpr (gr_fits(NT, 3)) if (sh.rg == 3) return launch_rows_t<KIND, GR_FULL, NT, 3>(a, blocks, s);

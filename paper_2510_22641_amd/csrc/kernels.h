@@ -268,14 +268,8 @@ struct ConfArgs {
 hipError_t launch_argmax_final(const float* part_val, const int* part_idx, int M, int n_parts,
                                int C, int32_t* dst0, int ld0, int off0, int32_t* dst1,
                                hipStream_t s);
-// The same, and the chosen token's embedding row (embed [vocab][d] in wdtype) into x_out row m.
-hipError_t launch_argmax_final_embed(const float* part_val, const int* part_idx, int M,
-                                     int n_parts, int C, int32_t* dst0, int ld0, int off0,
-                                     int32_t* dst1, const void* embed, int wdtype, int d,
-                                     float* x_out, hipStream_t s);
-
-// The general form: the chosen token's embedding row into x_out when embed is set, and the
-// confidence bookkeeping when cf.logits is set.
+// The general form: the chosen token's embedding row (embed [vocab][d] in wdtype) into x_out row m
+// when x_out is set, and the confidence bookkeeping when cf.logits is set.
 hipError_t launch_argmax_final_ex(const float* part_val, const int* part_idx, int M, int n_parts,
                                   int C, int32_t* dst0, int ld0, int off0, int32_t* dst1,
                                   const void* embed, int wdtype, int d, float* x_out,

@@ -18,8 +18,6 @@
 #include "gemv_common.h"
 #include "kernels.h"
 
-#include <hip/hip_ext.h>
-
 #include <climits>
 
 namespace ssd {
@@ -533,7 +531,7 @@ GvPlan gv_plan(const LinearArgs& a) {
 }
 
 template <typename WT, int MB, int KP>
-hipError_t launch_gemv_kp(const LinearArgs& a, const GvPlan& p, hipStream_t s, LaunchTiming* t) {
+hipError_t launch_gemv_kp(const LinearArgs& a, const GvPlan& p, hipStream_t s) {
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemv_kernel<WT, MB, KP>),
@@ -562,27 +560,27 @@ int gemv_pieces(int K) {
 namespace {
 
 template <typename WT, int MB>
-hipError_t launch_gemv_mb(const LinearArgs& a, const GvPlan& p, hipStream_t s, LaunchTiming* t) {
+hipError_t launch_gemv_mb(const LinearArgs& a, const GvPlan& p, hipStream_t s) {
   switch (gemv_pieces(a.K)) {
-    case 2: return launch_gemv_kp<WT, MB, 2>(a, p, s, t);
-    case 4: return launch_gemv_kp<WT, MB, 4>(a, p, s, t);
-    case 12: return launch_gemv_kp<WT, MB, 12>(a, p, s, t);
-    default: return launch_gemv_kp<WT, MB, 8>(a, p, s, t);
+    case 2: return launch_gemv_kp<WT, MB, 2>(a, p, s);
+    case 4: return launch_gemv_kp<WT, MB, 4>(a, p, s);
+    case 12: return launch_gemv_kp<WT, MB, 12>(a, p, s);
+    default: return launch_gemv_kp<WT, MB, 8>(a, p, s);
   }
 }
 
 template <typename WT>
-hipError_t launch_gemv_t(const LinearArgs& a, hipStream_t s, LaunchTiming* t) {
+hipError_t launch_gemv_t(const LinearArgs& a, hipStream_t s) {
   const GvPlan p = gv_plan(a);
   switch (p.mb) {
-    case 1: return launch_gemv_mb<WT, 1>(a, p, s, t);
-    case 2: return launch_gemv_mb<WT, 2>(a, p, s, t);
-    case 3: return launch_gemv_mb<WT, 3>(a, p, s, t);
-    case 4: return launch_gemv_mb<WT, 4>(a, p, s, t);
-    case 5: return launch_gemv_mb<WT, 5>(a, p, s, t);
-    case 6: return launch_gemv_mb<WT, 6>(a, p, s, t);
-    case 7: return launch_gemv_mb<WT, 7>(a, p, s, t);
-    default: return launch_gemv_mb<WT, 8>(a, p, s, t);
+    case 1: return launch_gemv_mb<WT, 1>(a, p, s);
+    case 2: return launch_gemv_mb<WT, 2>(a, p, s);
+    case 3: return launch_gemv_mb<WT, 3>(a, p, s);
+    case 4: return launch_gemv_mb<WT, 4>(a, p, s);
+    case 5: return launch_gemv_mb<WT, 5>(a, p, s);
+    case 6: return launch_gemv_mb<WT, 6>(a, p, s);
+    case 7: return launch_gemv_mb<WT, 7>(a, p, s);
+    default: return launch_gemv_mb<WT, 8>(a, p, s);
   }
 }
 
@@ -668,7 +666,7 @@ hipError_t launch_linear(LinearArgs a, hipStream_t s, int* n_parts, LaunchTiming
   const hipError_t e = launch_one_row(a, s, timing, &one);
   if (one) return e;
   if (dense_rows_ok(a)) return a.norm == NORM_LN ? launch_dense_rows<true>(a, s) : launch_dense_rows<false>(a, s);
-  return a.wdtype == 1 ? launch_gemv_t<bf16_t>(a, s, timing) : launch_gemv_t<float>(a, s, timing);
+  return a.wdtype == 1 ? launch_gemv_t<bf16_t>(a, s) : launch_gemv_t<float>(a, s);
 }
 
 }  // namespace ssd

@@ -327,15 +327,6 @@ hipError_t launch_argmax_final(const float* part_val, const int* part_idx, int M
                                 nullptr, 0, 0, nullptr, ConfArgs(), s);
 }
 
-hipError_t launch_argmax_final_embed(const float* part_val, const int* part_idx, int M,
-                                     int n_parts, int C, int32_t* dst0, int ld0, int off0,
-                                     int32_t* dst1, const void* embed, int wdtype, int d,
-                                     float* x_out, hipStream_t s) {
-  if (!embed || !x_out || d < 1) return hipErrorInvalidValue;
-  return launch_argmax_final_ex(part_val, part_idx, M, n_parts, C, dst0, ld0, off0, dst1, embed,
-                                wdtype, d, x_out, ConfArgs(), s);
-}
-
 hipError_t launch_read_probe(const void* buf, size_t bytes, float* out, hipStream_t s) {
   if (bytes < 16) return hipErrorInvalidValue;
   const size_t blocks = (bytes / 16 + 1023) / 1024;
