@@ -6,7 +6,7 @@ import pytest
 import synth
 from oracle.model import Decoder
 from oracle import decode
-from tests import parity
+from tests import parity, ring_forms
 
 pytestmark = pytest.mark.gpu
 
@@ -777,4 +777,21 @@ def test_imitation_network_on_rows_far_from_zero(batch, d_model):
     run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, reuse=True, max_rounds=1)
     assert dd.sync_status() == (0, 0)
     for s in sorted({0, batch - 1}):
+        parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=1)
+
+
+@pytest.mark.parametrize("wl", ring_forms.WORKLOADS, ids=lambda w: w.name)
+def test_many_row_kernel_on_every_form(wl):
+    """Passes of 130 to 900 rows whose projections take each tile form of the many-row kernel at
+    remainders of its columns and rows, with K ranges of unequal length (ring_forms says which; what the
+    last columns hold counts several times over, so that a wrong one moves every logit).  The first and
+    last sequence's prefill, draft and verify logits follow the oracle."""
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the forms were chosen for 256 compute units")
+    dd, dec, pr, z, pt, vt = _setup(wl, seed=81, batch=wl.batch, weights=ring_forms.stress_last_columns,
+                                    extra_seq=wl.gamma)
+    run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, max_rounds=1)
+    assert dd.sync_status() == (0, 0)
+    for s in (0, wl.batch - 1):
         parity.check_run_against_oracle(dec, wl.shape, pr[s], z[s], run, s, wl.gamma, max_rounds=1)
