@@ -8,8 +8,8 @@ stepwise calls token for token and round for round.  LLaVA-1.5-7B shape (c5): pr
 weights and needs tens of seconds per prefill there), and the whole 256-token job against the
 stepwise calls and the device's greedy decoding.  FlanT5-xl sweep points chosen by kernel
 path (one-row steps with 9-row verify chunks; batch 8 with 24- and 40-row verify chunks and
-72-row chunks on the two-plane skinny path): every sequence replayed for its first rounds, and
-every sequence of a batch against its own batch-1 run on the device.
+72-row chunks on the two-plane form of the few-row kernel): every sequence replayed for its first
+rounds, and every sequence of a batch against its own batch-1 run on the device.
 """
 import numpy as np
 import pytest
@@ -104,8 +104,8 @@ def _c4(b, k, g):
                          ids=["b1-k12-g8", "b8-k4-g8", "b8-k8-g2", "b8-k12-g4"])
 def test_c4_sweep_points(b, k, g, rounds):
     """Points of the FlanT5-xl sweep (one decoder, deep layers damped from layer 7 on), chosen by
-    kernel path: at batch 1 a 9-row verify chunk (two-plane skinny MFMA); at batch 8 the draft
-    steps are 8-row skinny launches and the verify chunk is 24, 40 or 72 rows, each sequence at
+    kernel path: at batch 1 a 9-row verify chunk (the few-row kernel's two-plane form); at batch 8 the
+    draft steps are 8-row launches and the verify chunk is 24, 40 or 72 rows, each sequence at
     its own length.  Every sequence is replayed through the oracle for its first rounds; the
     ssd_generate loop equals the stepwise calls token for token and round for round; and every
     sequence of the batch equals its own batch-1 run on the device up to a near-tie of the

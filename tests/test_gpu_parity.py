@@ -427,9 +427,9 @@ def test_folded_scores_from_layer_input_at_d2048():
 @pytest.mark.parametrize("heads,d_head", [(2, 128), (4, 64)], ids=["dh128", "dh64"])
 def test_long_prefix_prefill_splits_residual_projections_over_k(heads, d_head):
     """A LLaMA-style decoder with a 300-row visual prefix: the prefill's context block (307 rows)
-    is past the skinny capacity, so its projections take the tile GEMM, and the residual
-    projections (W_o, down) with few 128 x 128 tiles run over four ranges of K whose partial
-    products are added to the residual in range order; its causal self-attention takes the MFMA
+    is past the few-row kernel's 128, so its projections take the many-row kernel, and the down
+    projection (704 inputs) runs over four ranges of K whose partial products are added to the
+    residual in range order; its causal self-attention takes the MFMA
     kernel (five 64-row query tiles, keys in 64-key tiles, the last one ragged).  Prefill logits,
     drafts, verify logits and greedy steps follow the oracle."""
     from dataclasses import replace
@@ -464,9 +464,9 @@ def test_one_token_prompt_with_folded_cross_attention(width):
     assert dd.sync_status() == (0, 0)
 
 
-def test_verify_chunks_past_the_skinny_capacity_take_the_tile_path():
-    """Batch 8 with gamma = 16: a verify chunk is 8 x 17 = 136 rows, past the skinny path's 128, so
-    the verify's projections run on the tile GEMM (the residual ones over ranges of K) and each
+def test_verify_chunks_past_128_rows_take_the_many_row_kernel():
+    """Batch 8 with gamma = 16: a verify chunk is 8 x 17 = 136 rows, past the few-row kernel's 128, so
+    the verify's projections run on the many-row kernel (the down projection over ranges of K) and each
     sequence's 17-row causal self-attention on the MFMA kernel, its keys starting at that
     sequence's cached length.  Every sequence's drafts and verify logits follow the oracle round
     by round, with the accepted lengths bit-exact."""
@@ -481,24 +481,24 @@ def test_verify_chunks_past_the_skinny_capacity_take_the_tile_path():
 @pytest.mark.parametrize("arch,batch,d_ff", [("t5", 1, 8704), ("t5", 1, 5120), ("llama", 1, 8704),
                                              ("llama", 2, 8704), ("llama", 3, 8704)],
                          ids=["t5-b1", "t5-b1-ff5120", "llama-b1", "llama-b2", "llama-b3"])
-def test_wide_skinny_projections_share_input_loads_over_tiles(arch, batch, d_ff):
+def test_wide_projections_share_input_loads_over_tiles(arch, batch, d_ff):
     """Decoders 1536 wide: at a chunk of at most 8 rows on a 256-unit device the QKV projection
-    (288 tiles of 16 features) takes three half tiles a block (QKV epilogue with rotary or
-    without), a gated FFN 8704 wide (544 tiles) three whole tiles, one 5120 wide (320 tiles) three
-    half tiles of both matrices, and W_o, the cross-attention projections and the down projection
-    (96 tiles) one half tile.  Batch 2 also runs the draft steps (2 rows) on those paths; batch 3
-    verifies 12-row chunks on the two-plane form with several tiles a block.  Every sequence's
+    (288 tiles of 16 rows) takes two packed tiles a block of the few-row kernel (QKV epilogue with
+    rotary or without), a gated FFN 8704 or 5120 wide (1088 or 640 tiles of 8 features of both
+    matrices) three, and W_o, the cross-attention projections and the down projection (96 tiles) one
+    half tile.  Batch 2 also runs the draft steps (2 rows) on those forms; batch 3 verifies 12-row
+    chunks on the two-plane form with two and three tiles a block.  Every sequence's
     drafts, verify logits and accepted lengths follow the oracle."""
     from dataclasses import replace
     if arch == "t5":
-        sh = replace(synth.SMALL_T5_BF16, name="t5-wide-skinny", n_layers=3, d_model=1536,
+        sh = replace(synth.SMALL_T5_BF16, name="t5-wide", n_layers=3, d_model=1536,
                      n_heads=24, d_head=64, d_ff=d_ff, vocab=2000, n_visual=16)
-        wl = synth.S_T5.with_(name="s-t5-wide-skinny", shape=sh, draft_layers=2, gamma=5,
+        wl = synth.S_T5.with_(name="s-t5-wide", shape=sh, draft_layers=2, gamma=5,
                               new_tokens=16)
     else:
-        sh = replace(synth.SMALL_LLAMA_BF16, name="llama-wide-skinny", n_layers=3, d_model=1536,
+        sh = replace(synth.SMALL_LLAMA_BF16, name="llama-wide", n_layers=3, d_model=1536,
                      n_heads=12, d_head=128, d_ff=d_ff, vocab=2000, n_visual=24)
-        wl = synth.S_LLAMA.with_(name="s-llama-wide-skinny", shape=sh, draft_layers=2, gamma=3,
+        wl = synth.S_LLAMA.with_(name="s-llama-wide", shape=sh, draft_layers=2, gamma=3,
                                  new_tokens=16)
     # stepwise rounds keep drafting a finished sequence at its last length: gamma more positions
     dd, dec, pr, z, pt, vt = _setup(wl, seed=21, batch=batch, page_seed=9, extra_seq=wl.gamma)
@@ -544,7 +544,7 @@ def test_verify_chunk_folded_cross_attention(n_visual):
 @pytest.mark.parametrize("wl", [synth.S_T5, synth.S_LLAMA], ids=lambda w: w.name)
 def test_longest_draft_and_one_token_jobs(wl):
     """gamma = 32, the largest draft length a context accepts: the verify chunk is 33 rows, three
-    16-row groups of the two-plane skinny path with a one-row tail, and a round drafts 32 tokens
+    16-row groups of the few-row kernel's two-plane form, the last of one row, and a round drafts 32 tokens
     through the captured draft step.  Every draft and verify logit follows the oracle, the
     accepted lengths are bit-exact and the generate loop equals the stepwise calls.  A job of one
     token (T = 1) is the prefill's token alone: no round runs."""
@@ -564,12 +564,12 @@ def test_longest_draft_and_one_token_jobs(wl):
 
 
 @pytest.mark.parametrize("wl", [synth.S_T5, synth.S_LLAMA], ids=lambda w: w.name)
-def test_verify_chunk_at_the_skinny_capacity(wl):
-    """Batch 32 with gamma = 3: the verify chunk is 32 x 4 = 128 rows, the most the skinny MFMA
-    path takes (eight 16-row groups of the two-plane form), and the draft steps are 32-row skinny
-    launches; the T5 cross-attention runs unfolded (more than one sequence).  Every sequence's
-    drafts and verify logits follow the oracle round by round, with the accepted lengths
-    bit-exact, and the generate loop equals the stepwise calls."""
+def test_verify_chunk_of_128_rows(wl):
+    """Batch 32 with gamma = 3: the verify chunk is 32 x 4 = 128 rows, the most the few-row kernel
+    takes (eight 16-row groups of the two-plane form), and the draft steps are 32-row launches of it;
+    the T5 cross-attention runs unfolded (more than one sequence).  Every sequence's drafts and verify
+    logits follow the oracle round by round, with the accepted lengths bit-exact, and the generate loop
+    equals the stepwise calls."""
     wl = wl.with_(name=wl.name + "-b32", gamma=3, new_tokens=10)
     dd, dec, pr, z, pt, vt = _setup(wl, seed=23, batch=32, page_seed=9, extra_seq=wl.gamma)
     run = parity.device_run(dd, pt, vt, wl.new_tokens, wl.gamma, reuse=True)
