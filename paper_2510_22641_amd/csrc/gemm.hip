@@ -614,7 +614,12 @@ hipError_t launch_ring(const LinearArgs& a, int form, int n_out, hipStream_t s) 
   }
 }
 
-constexpr int ROWS_MAX = 128;  // rows the weight-streaming form takes
+// Rows the weight-streaming kernel takes.  Verify passes with it, and with the ring kernel in its place:
+// FlanT5-xl of 40, 72 and 128 rows 2283, 2582 and 3059 us against 3095, 2984 and 3474, FlanT5-base of
+// 128 rows 823 against 1135.  The line is drawn for such layers; with LLaVA-7B's (4096 wide) the two
+// meet at 36 to 48 rows (6299 and 6534 against 6148 and 6515) and 96 and 128 rows would be faster on
+// the ring kernel (8907 and 10237 against 8151 and 8530).
+constexpr int ROWS_MAX = 128;
 
 }  // namespace
 

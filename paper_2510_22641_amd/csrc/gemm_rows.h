@@ -438,7 +438,10 @@ hipError_t launch_rows_u(const LinearArgs& a, int blocks, hipStream_t s) {
 
 // Steps a batch: a wave's whole share of K when the registers hold it and the blocks are one round
 // (with more the extra registers would cost the blocks that run beside each other: the LM head of 6
-// rows 32 us against 36), else double-buffered batches of as many as they hold.
+// rows 32 us against 36), else double-buffered batches of as many as they hold.  One-batch depths are 2,
+// 4 and 10, to keep the instances few: a wave of 5 to 9 steps reads its last one again, from cache.
+// (Verify of 5 rows of four T5 layers 2560 wide, 5 steps a wave, 353 us; 445 with the kernel before,
+// whose depths were balanced.)
 template <int KIND, int MODE, int NT, int RG>
 hipError_t launch_rows_t(const LinearArgs& a, int blocks, hipStream_t s) {
   constexpr int one = gr_one(MODE, NT, RG), u = gr_batch(MODE, NT, RG);

@@ -74,7 +74,7 @@ struct LinearArgs {
   // EPI_ARGMAX
   float* part_val = nullptr;  // [M][n_parts]
   int* part_idx = nullptr;
-  int n_parts = 0;            // filled by argmax_parts()
+  int n_parts = 0;            // set by the launchers
   float* logits = nullptr;    // [M][ldl] or null
   int ldl = 0;
   // EPI_QKV: row m = b*C + j sits at position kv.seq_len[b] + kv.pos_off + j
@@ -158,8 +158,9 @@ int argmax_parts_max(int n_out);
 
 // Two rows and more with bf16 weights: the inputs arrive as bf16 planes written once by their
 // producer (a.in_planes ..., see LinearArgs), with RMSNorm folded (a.norm = NORM_RMS: the gain is
-// already in the planes, 1/rms from a.in_ssq) or none; the store, gated (to planes), QKV (rotary +
-// KV store), residual (+ next planes), bias and argmax epilogues.  K is a multiple of 64.
+// already in the planes, 1/rms from a.in_ssq) for the store, gated (to planes), QKV (rotary + KV store)
+// and argmax epilogues, or without a norm for the residual (+ next planes), bias and cross ones.  K is a
+// multiple of 64.
 // *n_parts: argmax partials per row; *n_ssq: partial sums of squares a residual epilogue leaves.
 hipError_t launch_linear_rows(const LinearArgs& a, hipStream_t s, int* n_parts = nullptr,
                               int* n_ssq = nullptr);
