@@ -168,11 +168,12 @@ int ssd_create(const ssd_dims* dims, const ssd_weights* w, const ssd_kv* kv, voi
  * another allocating routine, on the device or the host.  Dimensions whose workspace
  * (ssd_workspace_bytes without the folded matrices and, past 8 sequences, without the operand planes
  * of the imitation network's hidden features, which then stay float32 rows) exceeds
- * SSD_STATIC_SCRATCH_BYTES are refused with SSD_ERR_CAPACITY before anything runs.  At most one such context per device is alive at a
- * time (a second call before ssd_destroy of the first returns SSD_ERR_STATE): every context made
- * here on one GPU shares that GPU's array, which keeps the previous context's contents (this
- * call rebuilds the tables and clears the status word; every other slice is written before it
- * is read), and work of two of them that overlapped on one GPU would race. */
+ * SSD_STATIC_SCRATCH_BYTES are refused with SSD_ERR_CAPACITY before anything runs.  At most one
+ * such context per device is alive at a time (a second call before ssd_destroy of the first returns
+ * SSD_ERR_STATE): every context made here on one GPU shares that GPU's array, which keeps the
+ * previous context's contents (this call rebuilds the tables and clears the status word; every
+ * other slice is written before it is read), and work of two of them that overlapped on one GPU
+ * would race. */
 #define SSD_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 int ssd_create_static(const ssd_dims* dims, const ssd_weights* w, const ssd_kv* kv, void* stream,
                       ssd_ctx** out);
